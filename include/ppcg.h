@@ -240,7 +240,11 @@ typedef struct {
     int32_t col_index_bytes; /* bytes per stored column index the iteration's SpMV reads: 2 when
                                 every SELL column fits a 16-bit offset from its row, 0 when the
                                 PIPECG SpMV with FP64 vectors reads the chunks' shared offset
-                                lists (PPCG_FLAG_SELL_SHARED_OFFSETS), else 4 */
+                                lists (PPCG_FLAG_SELL_SHARED_OFFSETS), else 4.  0 and a
+                                value_bytes of 1 also stand for the single-launch form of
+                                constant-coefficient stencils, which reads lists of offsets,
+                                values and row masks per 64 rows and nothing per entry
+                                (bytes_per_iter counts that) */
     int32_t diag_const;      /* 1: every diagonal entry is equal; the fused update then reads
                                 the inverse diagonal as one cached value, not a vector */
     int32_t value_bytes;     /* bytes per stored value the iteration's SpMV reads: 1 with the

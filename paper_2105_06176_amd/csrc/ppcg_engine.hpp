@@ -117,6 +117,13 @@ struct ppcg_handle {
     int *cpat = nullptr, *pats = nullptr;
     int npats = 0;
     bool shared_on = false;
+    // chunks described by lists alone (ppcg_stencil.hpp), one allocation, or
+    // NULL; iterated by k_stencil in the single-launch form
+    int4 *schunk = nullptr;
+    int *soff = nullptr;
+    double *sval = nullptr;
+    unsigned long long *smask = nullptr;
+    ppcg::DevArena st_arena;
     int *perm = nullptr, *invperm = nullptr;
     double *val64 = nullptr;  // FP64 values in the stored format
     float *val32 = nullptr;   // FP32 copy of the stored values (mixed modes)
@@ -183,6 +190,8 @@ struct Job {
     bool pcg = false;
     // FP64 PIPECG in the single-launch form
     bool fused = false;
+    // ... on chunks described by lists (k_stencil)
+    bool stencil = false;
     // the initialisation has run once (a later one is a restart from x)
     bool started = false;
     // the initial guess is zero: the first initialisation needs no SpMV
@@ -208,6 +217,7 @@ struct Group {
     int prec = PREC_F64;
     bool pcg = false;               // iterates Algorithm 1 (two launches per iteration, PAR alternating)
     bool fused = false;             // FP64 PIPECG, one launch per iteration (work items are fused tiles)
+    bool stencil = false;           // ... of k_stencil instead of k_fused
     int cap_sys = 0;
     SysDesc *desc_d = nullptr;
     SysState *st_d = nullptr;
@@ -301,7 +311,7 @@ class Engine {
             return gp32_;
         if (j.pcg)
             return j.mixed == MIX_VALUES32 ? gpv_ : gp_;
-        return j.mixed == MIX_VALUES32 ? gv_ : j.small ? gs_ : j.fused ? gf_ : g64_;
+        return j.mixed == MIX_VALUES32 ? gv_ : j.small ? gs_ : j.stencil ? gt_ : j.fused ? gf_ : g64_;
     }
     int pslot(const Job &j) const { return j.mixed == MIX_INNER32 ? j.slot32 : j.mixed == MIX_VALUES32 ? j.slotv : j.slot64; }
     ppcg_status sync_states(Group &g);
@@ -311,14 +321,14 @@ class Engine {
     // the tables and auxiliary work, joined back before the poll), so the
     // groups' launches overlap: the one-workgroup small-system kernel and the
     // graphs of groups holding systems of different precision or method.
-    static constexpr int kGroups = 7;
+    static constexpr int kGroups = 8;
     hipStream_t gstream_[kGroups] = {};
     hipEvent_t ev_fork_ = nullptr;
     hipEvent_t ev_desc_ = nullptr;  // the last flush's descriptor copies (staging reuse)
     bool desc_copy_queued_ = false;
     hipEvent_t ev_join_[kGroups] = {};
     Group g64_, gv_, gs_;   // FP64 (and the FP64 steps of FP32-vector jobs), FP32 values, small systems
-    Group gf_;              // FP64 PIPECG in the single-launch form
+    Group gf_, gt_;         // FP64 PIPECG in the single-launch form: per-row storage, chunk lists
     Group gp_, gpv_, gp32_; // classic PCG: FP64, FP32 values, FP32 vectors
     std::vector<Job> jobs_;
 };
@@ -388,8 +398,9 @@ void launch_pipecg_iter(hipStream_t s, const WorkItem *tab, const int *cnt, cons
 void launch_pipecg_init_fused(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid,
                               bool x_zero = false);
 // K launches of the single-launch form over a table of fused tiles (K even),
-// preceded by k_fused_begin.
-void launch_fused_chunk(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int iters);
+// preceded by k_fused_begin; stencil: k_stencil instead of k_fused.
+void launch_fused_chunk(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int iters,
+                        bool stencil);
 // Allocate the single-launch form's buffers of a handle (once).
 ppcg_status ensure_fused(ppcg_handle *h);
 // Fused tiles of a handle's system (fused_tile_rows(n, cus) rows each).

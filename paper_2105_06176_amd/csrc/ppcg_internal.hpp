@@ -229,6 +229,12 @@ struct SysDesc {
     const int *cpat;      // SELL: start of each chunk's shared offset list in pats, when the FP64
                           // PIPECG SpMV reads them (else NULL)
     const int *pats;      // the distinct offset lists, concatenated
+    // chunks described by lists alone (ppcg_stencil.hpp): per chunk {list
+    // start, mask start, length, 0}, or NULL
+    const int4 *schunk;
+    const int *soff;      // byte offset of each list entry's column from the row
+    const double *sval;   // its value
+    const unsigned long long *smask;  // the lanes whose row has it
     const void *val;      // matrix values (double or float)
     const float *val32;   // FP32 copy of the values (vals32 mode)
     const void *dinv;     // inverse diagonal (double or float)

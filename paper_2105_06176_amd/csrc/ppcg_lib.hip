@@ -24,6 +24,7 @@
 #include <string>
 #include <thread>
 #include <tuple>
+#include <unordered_map>
 #include <vector>
 
 #include "ppcg_engine.hpp"
@@ -32,6 +33,7 @@
 #include "ppcg_small.hpp"
 #include "ppcg_setup.hpp"
 #include "ppcg_fused.hpp"
+#include "ppcg_stencil.hpp"
 
 namespace ppcg {
 
@@ -173,6 +175,9 @@ static ByteModel byte_model(const ppcg_handle *h, int prec)
     if (h->form == FORM_FUSED && prec == PREC_F64 && !pcg) {
         bm.vma -= (h->dinv_const ? 2.0 : 1.0) * ve * n;
         bm.spmv -= ve * n;
+        // chunks described by lists: 16 bytes per chunk stand for the matrix
+        if (h->schunk)
+            bm.spmv = 16.0 * h->nchunks + ve * n;
     }
     return bm;
 }
@@ -475,6 +480,12 @@ ppcg_status fill_desc(ppcg_handle *h, int prec, SysState *st, SysDesc *d, double
     d->nvtab = h->nvtab;
     d->cpat = h->shared_on ? h->cpat : nullptr;
     d->pats = h->pats;
+    if (prec == PREC_F64 && h->form == FORM_FUSED) {
+        d->schunk = h->schunk;
+        d->soff = h->soff;
+        d->sval = h->sval;
+        d->smask = h->smask;
+    }
     d->val = pd.val;
     d->val32 = h->val32;
     d->vals32 = vals32;
@@ -588,6 +599,15 @@ static ppcg_status time_spmv(ppcg_handle *h, int reps, double *ms)
     return PPCG_OK;
 }
 
+static void drop_stencil(ppcg_handle *h)
+{
+    h->st_arena.release();
+    h->schunk = nullptr;
+    h->soff = nullptr;
+    h->sval = nullptr;
+    h->smask = nullptr;
+}
+
 static void free_matrix(ppcg_handle *h)
 {
     if (h->cptr) (void)dev_free(h->cptr);
@@ -609,6 +629,7 @@ static void free_matrix(ppcg_handle *h)
     h->cpat = h->pats = nullptr;
     h->npats = 0;
     h->shared_on = false;
+    drop_stencil(h);
     h->cptr = nullptr;
     h->rp = h->col = h->perm = h->invperm = nullptr;
     h->val64 = nullptr;
@@ -963,9 +984,9 @@ static std::map<std::tuple<int, int, int, int>, bool> g_shared_kept;
 
 static ppcg_status tune_shared(ppcg_handle *h)
 {
-    h->shared_on = false;
+    h->shared_on = h->schunk != nullptr;
     const unsigned fl = h->opt.flags;
-    if (!h->cpat || h->fmt != FMT_SELL || (fl & PPCG_FLAG_SELL_NO_SHARED_OFFSETS))
+    if (h->schunk || !h->cpat || h->fmt != FMT_SELL || (fl & PPCG_FLAG_SELL_NO_SHARED_OFFSETS))
         return PPCG_OK;
     if (fl & PPCG_FLAG_SELL_SHARED_OFFSETS) {
         h->shared_on = true;
@@ -1013,6 +1034,106 @@ static void shared_for_fused(ppcg_handle *h)
     if (h->form == FORM_FUSED && h->cpat && !h->shared_on &&
         !(fl & (PPCG_FLAG_SELL_NO_SHARED_OFFSETS | PPCG_FLAG_SELL_COL16 | PPCG_FLAG_SELL_COL32)))
         h->shared_on = true;
+}
+
+// Describe the chunks by lists alone (ppcg_stencil.hpp) when every one
+// qualifies: rows in their own order on shared offset lists, one value per
+// list entry, a constant diagonal, the value table kept and neither a column
+// layout nor the two-launch form pinned.  The distinct lists may take at most
+// half the bytes of the one-byte value indices that the lists replace
+// (or 64 KiB): a wavefront reads them through the scalar cache, and matrices
+// whose chunks are mostly of different kinds gain nothing.
+static ppcg_status build_stencil(ppcg_handle *h)
+{
+    const unsigned fl = h->opt.flags;
+    if (h->fmt != FMT_SELL || !h->cpat || h->perm || !h->vidx || !h->dinv_const || h->n > kStMaxRows ||
+        (h->n <= PPCG_SMALL_MAX_ROWS && !(fl & PPCG_FLAG_ITER_FUSED)) ||
+        (fl & (PPCG_FLAG_SELL_COL16 | PPCG_FLAG_SELL_COL32 | PPCG_FLAG_SELL_NO_SHARED_OFFSETS |
+               PPCG_FLAG_ITER_TWO_LAUNCH)) != 0)
+        return PPCG_OK;
+    hipStream_t s = h->stream;
+    const int nc = h->nchunks;
+    const int64_t nl = h->nnz_stored / kSellC;
+    if (nl < 1)
+        return PPCG_OK;
+    // scratch: per list entry a value and a mask, per chunk two hashes and
+    // the representatives to copy, a flag.  It stays with the lists where
+    // both are small (an allocation and a release, which waits for the
+    // device, fewer per handle), else it is released here.
+    DevArena tmp;
+    struct Free {
+        DevArena &a;
+        ~Free() { a.release(); }
+    } free_tmp{tmp};
+    const size_t scratch = 16 * (size_t)nl + (16 + 32) * (size_t)nc + 8 * 256;
+    const size_t most = 16 * (size_t)nc + 20 * (size_t)nl + 8 * 256;
+    const bool keep = scratch + most <= (1u << 20);
+    DevArena &sa = keep ? h->st_arena : tmp;
+    PPCG_TRY(sa.alloc(keep ? scratch + most : scratch));
+    double *tval = (double *)sa.take(8 * (size_t)nl);
+    unsigned long long *tmask = (unsigned long long *)sa.take(8 * (size_t)nl);
+    unsigned long long *hash = (unsigned long long *)sa.take(16 * (size_t)nc);
+    int4 *items_d = (int4 *)sa.take(32 * (size_t)nc);
+    unsigned *flag = (unsigned *)sa.take(sizeof(unsigned));
+    std::vector<unsigned long long> hh(2 * (size_t)nc);
+    std::vector<int64_t> cp((size_t)nc + 1);
+    unsigned bad = 0u;
+    k_fill<unsigned><<<1, 64, 0, s>>>(1, flag, 0u);
+    k_st_scan<<<nc, kSellC, 0, s>>>(nc, h->cptr, h->cpat, h->pats, h->val64, tval, tmask, hash, flag);
+    PPCG_HIP(hipGetLastError());
+    PPCG_HIP(hipMemcpyAsync(&bad, flag, sizeof bad, hipMemcpyDeviceToHost, s));
+    PPCG_HIP(hipMemcpyAsync(hh.data(), hash, 16 * (size_t)nc, hipMemcpyDeviceToHost, s));
+    PPCG_HIP(hipMemcpyAsync(cp.data(), h->cptr, sizeof(int64_t) * cp.size(), hipMemcpyDeviceToHost, s));
+    PPCG_HIP(hipStreamSynchronize(s));
+    if (bad)
+        return PPCG_OK;
+    std::unordered_map<unsigned long long, int> lists, masks;
+    std::vector<int4> chunk((size_t)nc), items;
+    int64_t nlist = 0, nmask = 0;
+    const int64_t cap = std::max<int64_t>(h->nnz_stored / 2, 65536);
+    for (int c = 0; c < nc; ++c) {
+        const int len = (int)((cp[c + 1] - cp[c]) / kSellC);
+        const auto l = lists.emplace(hh[2 * (size_t)c], (int)nlist);
+        const auto m = masks.emplace(hh[2 * (size_t)c + 1], (int)nmask);
+        if (l.second) {
+            items.push_back(make_int4(c, (int)nlist, 0, 0));
+            nlist += len;
+        }
+        if (m.second) {
+            items.push_back(make_int4(c, (int)nmask, 1, 0));
+            nmask += len;
+        }
+        if (12 * nlist + 8 * nmask > cap)
+            return PPCG_OK;
+        chunk[c] = make_int4(l.first->second, m.first->second, len, 0);
+    }
+    if (!keep)
+        PPCG_TRY(h->st_arena.alloc(16 * (size_t)nc + 12 * (size_t)nlist + 8 * (size_t)nmask + 8 * 256));
+    int4 *schunk = (int4 *)h->st_arena.take(16 * (size_t)nc);
+    h->sval = (double *)h->st_arena.take(8 * (size_t)std::max<int64_t>(nlist, 1));
+    h->smask = (unsigned long long *)h->st_arena.take(8 * (size_t)std::max<int64_t>(nmask, 1));
+    h->soff = (int *)h->st_arena.take(4 * (size_t)std::max<int64_t>(nlist, 1));
+    hipError_t e = hipMemcpyAsync(schunk, chunk.data(), 16 * (size_t)nc, hipMemcpyHostToDevice, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(items_d, items.data(), 16 * items.size(), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) {
+        k_st_copy<<<(unsigned)items.size(), 64, 0, s>>>(items_d, h->cptr, h->cpat, h->pats, tval, tmask, h->soff,
+                                                         h->sval, h->smask);
+        k_st_verify<<<nc, 64, 0, s>>>(nc, h->cptr, h->cpat, h->pats, tval, tmask, schunk, h->soff, h->sval,
+                                      h->smask, flag);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(&bad, flag, sizeof bad, hipMemcpyDeviceToHost, s);
+    const hipError_t es = hipStreamSynchronize(s);
+    if (e == hipSuccess)
+        e = es;
+    if (e != hipSuccess || bad)  // bad: two different lists of one hash
+        drop_stencil(h);
+    else
+        h->schunk = schunk;
+    PPCG_HIP(e);
+    return PPCG_OK;
 }
 
 // ---------------------------------------------------------------- iteration form
@@ -1102,7 +1223,7 @@ static ppcg_status tune_form(ppcg_handle *h)
     const uint32_t f = h->opt.flags;
     if ((f & PPCG_FLAG_ITER_TWO_LAUNCH) || h->fmt != FMT_SELL)
         return PPCG_OK;
-    if (f & PPCG_FLAG_ITER_FUSED) {
+    if ((f & PPCG_FLAG_ITER_FUSED) || h->schunk) {
         PPCG_TRY(ensure_fused(h));
         h->form = FORM_FUSED;
         return PPCG_OK;
@@ -1398,7 +1519,7 @@ Engine::~Engine()
         if (ev_join_[k]) (void)hipEventDestroy(ev_join_[k]);
     }
     if (ev_fork_) (void)hipEventDestroy(ev_fork_);
-    for (Group *g : {&g64_, &gv_, &gs_, &gp_, &gpv_, &gp32_, &gf_}) {
+    for (Group *g : {&g64_, &gv_, &gs_, &gp_, &gpv_, &gp32_, &gf_, &gt_}) {
         drop_graphs(*g);
         if (g->desc_d) (void)dev_free(g->desc_d);
         if (g->st_d) (void)dev_free(g->st_d);
@@ -1469,8 +1590,10 @@ ppcg_status Engine::init(int cap_sys)
     PPCG_TRY(ensure_group(gpv_, PREC_V32, cap_sys));
     PPCG_TRY(ensure_group(gp32_, PREC_F32, cap_sys));
     PPCG_TRY(ensure_group(gf_, PREC_F64, cap_sys));
+    PPCG_TRY(ensure_group(gt_, PREC_F64, cap_sys));
     gp_.pcg = gpv_.pcg = gp32_.pcg = true;
-    gf_.fused = true;
+    gf_.fused = gt_.fused = true;
+    gt_.stencil = true;
     return PPCG_OK;
 }
 
@@ -1500,7 +1623,7 @@ ppcg_status Engine::upload_desc(Group &g, int slot)
 // of systems thus costs a few transfers instead of two per system.
 ppcg_status Engine::flush_uploads()
 {
-    Group *const groups[] = {&g64_, &gv_, &gs_, &gp_, &gpv_, &gp32_, &gf_};
+    Group *const groups[] = {&g64_, &gv_, &gs_, &gp_, &gpv_, &gp32_, &gf_, &gt_};
     bool copies = false;
     for (Group *g : groups) {
         for (int a = 0; a < g->cap_sys;) {
@@ -1615,11 +1738,22 @@ void launch_pipecg_init_fused(hipStream_t s, const WorkItem *tab, const int *cnt
     k_spmv<double, MODE_INIT2><<<grid, kSpmvThreads, 0, s>>>(tab, cnt, dd, rs);
 }
 
-void launch_fused_chunk(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int iters)
+// One launch of the single-launch form with parity i & 1.
+static void launch_fused(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int i,
+                         bool stencil)
+{
+    if (stencil)
+        k_stencil<<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1);
+    else
+        k_fused<<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1);
+}
+
+void launch_fused_chunk(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int iters,
+                        bool stencil)
 {
     k_fused_begin<<<grid, 64, 0, s>>>(tab, cnt, dd);
     for (int i = 0; i < iters; ++i)
-        k_fused<<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1);
+        launch_fused(s, tab, cnt, dd, grid, i, stencil);
 }
 
 void launch_true_resid(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid)
@@ -1745,7 +1879,7 @@ ppcg_status Engine::ensure_graph(Group &g, int iters, hipGraphExec_t *exec)
     Group::CapturedGraph cg;
     PPCG_HIP(hipStreamBeginCapture(stream_, hipStreamCaptureModeThreadLocal));
     if (g.fused)
-        launch_fused_chunk(stream_, g.table_d, g.count_d, g.desc_d, grid, iters);
+        launch_fused_chunk(stream_, g.table_d, g.count_d, g.desc_d, grid, iters, g.stencil);
     else
         for (int i = 0; i < iters; ++i)
             launch_iter_pair(stream_, g, grid, remap);
@@ -2015,19 +2149,21 @@ ppcg_status Engine::add(ppcg_handle *h, int mixed, double tol, const double *, i
         j.stage = JS_NEED_INIT;
     } else if (mixed == MIX_NONE && h->form == FORM_FUSED && h->frec && h->fmt == FMT_SELL) {
         j.fused = true;
-        j.slot64 = alloc_slot(gf_);
+        j.stencil = h->schunk != nullptr;
+        Group &g = j.stencil ? gt_ : gf_;
+        j.slot64 = alloc_slot(g);
         if (j.slot64 < 0) {
             set_error("engine has no free slot");
             return PPCG_ERR_INVALID_ARG;
         }
-        ppcg_status rc = fill_desc(h, PREC_F64, gf_.st_d + j.slot64, &gf_.desc_h[j.slot64], tol, o.fixed_iters,
+        ppcg_status rc = fill_desc(h, PREC_F64, g.st_d + j.slot64, &g.desc_h[j.slot64], tol, o.fixed_iters,
                                    o.max_iter, stop);
         if (rc != PPCG_OK) {
-            gf_.slot_used[j.slot64] = 0;
+            g.slot_used[j.slot64] = 0;
             return rc;
         }
-        PPCG_TRY(upload_desc(gf_, j.slot64));
-        clear_state(gf_, j.slot64);
+        PPCG_TRY(upload_desc(g, j.slot64));
+        clear_state(g, j.slot64);
         j.stage = JS_NEED_INIT;
     } else if (mixed == MIX_NONE && h->fmt == FMT_SELL && h->n <= PPCG_SMALL_MAX_ROWS) {
         j.small = true;
@@ -2118,7 +2254,8 @@ void Engine::retire(int id)
 {
     Job &j = jobs_[id];
     if (j.slot64 >= 0)
-        (j.pcg && j.mixed != MIX_INNER32 ? gp_ : j.small ? gs_ : j.fused ? gf_ : g64_).slot_used[j.slot64] = 0;
+        (j.pcg && j.mixed != MIX_INNER32 ? gp_ : j.small ? gs_ : j.stencil ? gt_ : j.fused ? gf_ : g64_)
+            .slot_used[j.slot64] = 0;
     if (j.slot32 >= 0)
         gp32_.slot_used[j.slot32] = 0;
     if (j.slotv >= 0)
@@ -2150,7 +2287,7 @@ ppcg_status Engine::step(int graph_iters)
     PPCG_TRY(flush_uploads());
     // 1. Jobs that need a true residual: stopped FP64 / FP32-values jobs, and
     //    FP32-vector jobs at a pause of their sequence (after adding the correction).
-    Group *const groups[] = {&g64_, &gv_, &gs_, &gp_, &gpv_, &gp32_, &gf_};
+    Group *const groups[] = {&g64_, &gv_, &gs_, &gp_, &gpv_, &gp32_, &gf_, &gt_};
     std::map<Group *, std::vector<int>> resid;  // slots per group
     std::vector<int> correct64;                 // FP64 slots of FP32-vector jobs
     for (Job &j : jobs_) {
@@ -2795,6 +2932,7 @@ ppcg_status ppcg_create(const ppcg_csr *A, const ppcg_options *opt, void *hip_st
     CKS(alloc_f64_vectors(h));
     CKS(choose_format(h, rp, ci, val, rowlen, dinv_orig, rowlen_h));
     CKS(tune_vtab(h, A->mem == PPCG_MEM_HOST ? A->values : nullptr, val));
+    CKS(build_stencil(h));
     CKS(tune_shared(h));
     CKS(tune_form(h));
     shared_for_fused(h);
@@ -3001,7 +3139,7 @@ ppcg_status ppcg_get_matrix_info(const ppcg_handle *h, ppcg_matrix_info *mi)
                        (h->fmt == FMT_SELL ? 8.0 * (h->nchunks + 1) : 4.0 * (h->n + 1)) +
                        (h->perm ? 8.0 * h->n : 0.0) + (h->col16 ? 2.0 * (double)h->nnz_stored : 0.0) +
                        (h->vidx ? (double)h->nnz_stored + 8.0 * h->nvtab : 0.0) +
-                       (h->cpat ? 4.0 * (h->nchunks + h->npats) : 0.0);
+                       (h->cpat ? 4.0 * (h->nchunks + h->npats) : 0.0) + (double)h->st_arena.size;
     mi->setup_ms = h->setup_ms;
     mi->col_index_bytes =
         h->shared_on ? 0
@@ -3066,12 +3204,14 @@ ppcg_status ppcg_time_kernels(ppcg_handle *h, const double *b, int32_t iters, do
         const int fgrid = fused_tiles(h);
         launch_pipecg_init_fused(s, tab, cnt, dd, grid);
         k_fused_begin<<<fgrid, 64, 0, s>>>(tab, cnt + 1, dd);
-        k_fused<<<fgrid, kFusedThreads, 0, s>>>(tab, cnt + 1, dd, PPCG_FUSED_REMAP, 0);
+        const bool stencil = h->schunk != nullptr;
+        launch_fused(s, tab, cnt + 1, dd, fgrid, 0, stencil);
         for (auto &e : ev)
             PPCG_HIP_CLEAN(hipEventCreate(&e), clean());
         for (int i = 1; i <= iters; ++i)
-            hipExtLaunchKernelGGL(k_fused, dim3(fgrid), dim3(kFusedThreads), 0, s, ev[4 * (i - 1)],
-                                  ev[4 * (i - 1) + 1], 0, tab, cnt + 1, dd, (int)PPCG_FUSED_REMAP, i & 1);
+            hipExtLaunchKernelGGL(stencil ? k_stencil : k_fused, dim3(fgrid), dim3(kFusedThreads), 0, s,
+                                  ev[4 * (i - 1)], ev[4 * (i - 1) + 1], 0, tab, cnt + 1, dd, (int)PPCG_FUSED_REMAP,
+                                  i & 1);
         PPCG_HIP_CLEAN(hipGetLastError(), clean());
         PPCG_HIP_CLEAN(hipStreamSynchronize(s), clean());
         double tf = 0;

@@ -1,0 +1,121 @@
+"""The single-launch iteration on chunks described by lists alone (offsets,
+values and lane masks per 64 rows) against the oracle and, bit for bit,
+against the same iteration on per-entry columns.
+
+The rows of both storages add the same products in the same order (a missing
+entry adds an exact zero), so equality is exact; against the oracle the
+iterates are held to the 1e-10 bar of every fixed-iteration test.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2105_06176_amd import ppcg
+from paper_2105_06176_amd.ppcg import Solver, solve_batch
+from workloads import CSR, poisson2d, poisson3d, poisson125, rhs_from_solution, shifted, xstar_uniform
+from workloads.gen import _constant_stencil
+
+pytestmark = pytest.mark.gpu
+
+FORM = ppcg.FLAG_ITER_FUSED | ppcg.FLAG_SELL_VALUE_TABLE
+LISTS, COLUMNS = FORM | ppcg.FLAG_SELL_SHARED_OFFSETS, FORM | ppcg.FLAG_SELL_NO_SHARED_OFFSETS
+
+
+def dev(a):
+    import torch
+
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float64)).cuda()
+
+
+def host(t):
+    return t.cpu().numpy()
+
+
+def tridiagonal(n, off, diag=4.0):
+    """off[i] couples rows i and i + 1; an entry is stored also where it is 0."""
+    import scipy.sparse as sp
+
+    M = sp.diags([np.ones(n - 1), np.ones(n), np.ones(n - 1)], [-1, 0, 1], format="csr")
+    M.sort_indices()
+    rows = np.repeat(np.arange(n), np.diff(M.indptr))
+    lo = np.minimum(rows, M.indices)
+    val = np.where(rows == M.indices, diag, np.append(off, 0.0)[lo])
+    return CSR(n, M.indptr.astype(np.int32), M.indices.astype(np.int32), val.astype(np.float64), f"tri{n}")
+
+
+def box(nx, ny, nz):
+    offs = [(0, 0, -1), (0, -1, 0), (-1, 0, 0), (0, 0, 0), (1, 0, 0), (0, 1, 0), (0, 0, 1)]
+    return _constant_stencil((nx, ny, nz), offs, 6.5, -1.0, f"box_{nx}_{ny}_{nz}")
+
+
+def halves(n, cut):
+    """Off-diagonals -1 before row `cut`, -0.5 after it."""
+    return tridiagonal(n, np.where(np.arange(n - 1) < cut, -1.0, -0.5))
+
+
+def stored_zeros(n):
+    off = np.full(n - 1, -1.0)
+    off[::7] = 0.0
+    off[3::11] = -0.0
+    return tridiagonal(n, off)
+
+
+# matrix, iterations, whether each entry of a chunk's list has one value
+CASES = {
+    "one_row": (lambda: CSR(1, np.array([0, 1], np.int32), np.zeros(1, np.int32), np.array([2.0])), 1, True),
+    "65_rows": (lambda: tridiagonal(65, np.full(64, -1.0)), 5, True),
+    "diagonal_only": (lambda: CSR(5000, np.arange(5001, dtype=np.int32), np.arange(5000, dtype=np.int32),
+                                  np.full(5000, 3.0)), 1, True),
+    "poisson2d_67": (lambda: poisson2d(67), 30, True),
+    "poisson2d_301": (lambda: poisson2d(301), 25, True),
+    "poisson3d_17": (lambda: poisson3d(17), 12, True),
+    "lines_of_3": (lambda: box(3, 40, 30), 15, True),
+    "lines_of_64": (lambda: box(64, 9, 11), 15, True),
+    "lines_of_63": (lambda: box(63, 9, 11), 15, True),
+    "poisson125_40": (lambda: poisson125(40), 8, True),
+    "halves_on_a_chunk_border": (lambda: halves(6400, 3199), 20, False),  # the entry 3199-3200 crosses the chunks
+    "halves_inside_a_chunk": (lambda: halves(6400, 3220), 20, False),
+    "stored_zeros": (lambda: stored_zeros(5003), 20, False),  # -0.0 is a value of its own beside -1
+    "five_rows_per_thread": (lambda: poisson3d(124), 5, True),
+}
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_lists_equal_columns_and_oracle(name):
+    gen, k, lists = CASES[name]
+    A = gen()
+    b = rhs_from_solution(A, xstar_uniform(A.n, 3))
+    S = Solver(A, fixed_iters=k, spmv_format="sell", flags=LISTS)
+    N = Solver(A, fixed_iters=k, spmv_format="sell", flags=COLUMNS)
+    mi = S.matrix_info()
+    if A.n > 64:  # beside the gathered vector: 16 bytes per 64 rows, or at least one per entry
+        per_row = (mi["bytes_spmv"] - 8.0 * A.n) / A.n
+        assert (per_row < 0.9) == (lists and mi["col_index_bytes"] == 0), per_row
+    if name.startswith("poisson2d") or "125" in name:
+        assert mi["col_index_bytes"] == 0
+    x, info = S.solve(dev(b))
+    y, _ = N.solve(dev(b))
+    ref = oracle.pipecg(A, b, fixed_iters=k)
+    assert info["status"] == ppcg.OK and info["iters"] == ref.iters
+    assert np.array_equal(host(x), host(y))
+    assert np.linalg.norm(host(x) - ref.x) <= 1e-10 * np.linalg.norm(ref.x)
+    for s in (S, N):
+        s.close()
+
+
+def test_batch_of_list_and_column_systems_equals_solo_bitwise():
+    """Both kernels in one batch, twice (captured graphs replayed), with systems that end at different times."""
+    mats = [poisson2d(80), shifted(poisson2d(121), 0.3), poisson3d(33), box(31, 17, 20), poisson2d(40)]
+    flags = [0, LISTS, COLUMNS, 0, 0]
+    bs = [rhs_from_solution(A, xstar_uniform(A.n, 9 + i)) for i, A in enumerate(mats)]
+    solvers = [Solver(A, tol=1e-10, spmv_format="sell", flags=f) for A, f in zip(mats, flags)]
+    solo = [s.solve(dev(b)) for s, b in zip(solvers, bs)]
+    for _ in range(2):
+        xs, infos = solve_batch(solvers, [dev(b) for b in bs])
+        for A, b, x, info, (sx, si) in zip(mats, bs, xs, infos, solo):
+            assert np.array_equal(host(x), host(sx)) and info["iters"] == si["iters"], A.name
+            assert oracle.true_relres(A, b, host(x)) <= 1e-10
+            assert abs(info["iters"] - oracle.pipecg(A, b, tol=1e-10).iters) <= 2
+    for s in solvers:
+        s.close()
