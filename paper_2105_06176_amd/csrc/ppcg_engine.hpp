@@ -151,6 +151,7 @@ struct ppcg_handle {
     ppcg::SysState *frec = nullptr;
     double *fpart = nullptr;
     double *w1 = nullptr;
+    double *shist = nullptr;  // k_stencil's alpha and beta since the last update of x
     ppcg::DevArena fused_arena;
 };
 

@@ -159,6 +159,25 @@ static_assert(kFusedThreads % kSellC == 0, "each wavefront of a fused tile reads
 #define PPCG_SMALL_MAX_ROWS 4096
 #endif
 
+// k_stencil's update of p and x (ppcg_stencil.hpp).  p feeds nothing but x:
+// with the ring, the last kStDefer residuals are kept (each is written to a
+// buffer of its own anyway) and p and x are brought up to date once in
+// kStDefer launches, the same operations in the same order.  Bytes per row
+// and launch: 78 against 88 with p updated in every launch and x in every
+// second; but ten vectors are live instead of seven, and while they all fit
+// the 256 MiB memory-side cache that counts for more than the bytes.
+// Measured, ring against none, us per iteration: 100^3 17.4 / 19.3, 128^3
+// 29.5 / 33.0, 1800^2 (3.24 M rows: ten vectors just fit) 50.7 / 53.4, 160^3
+// (4.1 M rows: seven fit) 70.4 / 64.0, 176^3 (5.5 M rows: neither) 99.5 /
+// 115.6, 200^3 146.9 / 167.9.
+constexpr int kStDefer = 4;
+constexpr double kCacheBytes = 256.0 * 1024 * 1024;
+inline bool stencil_ring(int n)
+{
+    return 10 * 8.0 * n <= kCacheBytes || 7 * 8.0 * n > kCacheBytes;
+}
+constexpr int kStHist = 32;  // doubles between its two slots of past scalars (256 bytes)
+
 enum Fmt : int { FMT_SELL = 1, FMT_CSRV = 2 };
 enum Prec : int { PREC_F64 = 0, PREC_F32 = 1, PREC_V32 = 2 /* FP32 values, FP64 vectors */ };
 
@@ -235,6 +254,9 @@ struct SysDesc {
     const int *soff;      // byte offset of each list entry's column from the row
     const double *sval;   // its value
     const unsigned long long *smask;  // the lanes whose row has it
+    double *shist;        // 2 slots (launch parity) of alpha[kStDefer], beta[kStDefer]
+    int vstride;          // bytes between two of the FP64 vectors x r u w m nv z q s p
+    int sring;            // 1: k_stencil keeps kStDefer residuals and updates p and x together
     const void *val;      // matrix values (double or float)
     const float *val32;   // FP32 copy of the values (vals32 mode)
     const void *dinv;     // inverse diagonal (double or float)

@@ -20,18 +20,25 @@
 // value is replaced by 0, and the row sum adds the same products in the same
 // order as the per-entry storage (whose missing entries are explicit zeros).
 //
-// Bound by the vector streams (96 bytes per row and iteration) on short rows
-// and by the gathers on long ones.  Measured against k_fused on the one-byte
-// value table, per iteration: 128^3 7-point 51.1 -> 33.5 us, 165^3 125-point
-// 480 -> 300 us, 301^2 5-point 7.4 -> 6.7 us.
+// Bound by the vector streams on short rows and by the gathers on long ones.
+// Measured, us per iteration, k_fused on the one-byte value table, then with
+// the chunk lists, then also with the ring of residuals (kStDefer): 128^3
+// 7-point 49.4, 32.0, 29.5 (164 MB in the last: 5.6 TB/s, of which about
+// 5 us are the launch's start and its reduction); 100^3 26.7, 18.6, 17.4;
+// 165^3 125-point 471, 278, 278 (no ring at that size); 301^2 5-point 6.6,
+// 5.8, 5.8.  Streaming hints (nt) on the loads or stores: 36 to 44 us at
+// 128^3, because the vectors then miss the memory-side cache.  Forming z from
+// s in every launch (z = A M^-1 s, gathered beside w, instead of z carried;
+// 16 bytes per row fewer) measured no faster at 7 points and twice slower at
+// 125: the second gather costs what the stream saves.
 #pragma once
 
 #include "ppcg_fused.hpp"
 
 namespace ppcg {
 
-// Largest system: byte offsets of rows and columns fit 31 bits.
-constexpr int kStMaxRows = (1 << 28) - (1 << 14);
+// Largest system: the byte offsets of ten vectors fit 31 bits.
+constexpr int kStMaxRows = 25000000;
 
 // ---------------------------------------------------------------- setup
 __device__ __forceinline__ unsigned long long st_mix(unsigned long long h, unsigned long long v)
@@ -145,6 +152,9 @@ __device__ __forceinline__ double st_load(StBuf b, int byte)
     return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, byte, 0, 0));
 }
 
+// A chunk's list start, mask start and length.
+typedef int StChunk __attribute__((ext_vector_type(4)));
+
 // One chunk's lists (uniform over the wavefront).
 struct StLists {
     const __attribute__((address_space(4))) int *off;
@@ -152,11 +162,11 @@ struct StLists {
     const __attribute__((address_space(4))) unsigned long long *mask;
 };
 
-// Entries k0 .. k0 + L - 1 of a row: the L gathers back to back, then their
+// Entries k0 .. k0 + L - 1 of a row: the gathers back to back, then their
 // products added in entry order; each is value * (d0 * w[col]), m = M^-1 w
 // formed from the gathered w as everywhere in the single-launch form.
 template <int L>
-__device__ __forceinline__ void st_span(const StLists &p, int k0, StBuf w, int rowb, double d0, double &n)
+__device__ __forceinline__ double st_span(const StLists p, int k0, StBuf w, int rowb, double d0, double a)
 {
     double x[L];
 #pragma unroll
@@ -165,44 +175,66 @@ __device__ __forceinline__ void st_span(const StLists &p, int k0, StBuf w, int r
 #pragma unroll
     for (int j = 0; j < L; ++j) {
         const bool has = __builtin_amdgcn_inverse_ballot_w64(p.mask[k0 + j]);
-        n = n + p.val[k0 + j] * (d0 * (has ? x[j] : 0.0));
+        a = a + p.val[k0 + j] * (d0 * (has ? x[j] : 0.0));
     }
+    return a;
 }
 
 template <int M>
-__device__ __forceinline__ void st_tail(int rem, const StLists &p, int k0, StBuf w, int rowb, double d0, double &n)
+__device__ __forceinline__ double st_tail(int rem, const StLists p, int k0, StBuf w, int rowb, double d0, double a)
 {
     if constexpr (M > 0) {
         if (rem == M)
-            st_span<M>(p, k0, w, rowb, d0, n);
-        else
-            st_tail<M - 1>(rem, p, k0, w, rowb, d0, n);
+            return st_span<M>(p, k0, w, rowb, d0, a);
+        return st_tail<M - 1>(rem, p, k0, w, rowb, d0, a);
+    } else {
+        return a;
     }
 }
 
-// (A m)[row] of one lane's row: ch = the chunk's list start, mask start and
-// length (uniform).
-__device__ __forceinline__ double st_row(const SysDesc &d, int lst, int msk, int len, StBuf w, int rowb, double d0)
+// (A m)[row] of one lane's row of chunk ch.
+__device__ __forceinline__ double st_row(const SysDesc &d, StChunk ch, StBuf w, int rowb, double d0)
 {
     constexpr int B = 8;
-    const StLists p{as_constant(d.soff) + lst, as_constant(d.sval) + lst, as_constant(d.smask) + msk};
-    double n = 0.0;
+    const int len = ch[2];
+    const StLists p{as_constant(d.soff) + ch[0], as_constant(d.sval) + ch[0], as_constant(d.smask) + ch[1]};
+    double a = 0.0;
     int k0 = 0;
     for (; k0 + B <= len; k0 += B)
-        st_span<B>(p, k0, w, rowb, d0, n);
-    st_tail<B - 1>(len - k0, p, k0, w, rowb, d0, n);
-    return n;
+        a = st_span<B>(p, k0, w, rowb, d0, a);
+    return st_tail<B - 1>(len - k0, p, k0, w, rowb, d0, a);
+}
+
+struct StScalars {
+    double alpha, beta;
+    double hist[2 * kStDefer];  // alpha, beta of the updates since the last full ring
+    int go;
+};
+
+// The handle's vectors lie in one allocation at a fixed distance: one buffer
+// resource and a scalar offset name any of them, where a pointer each would
+// not fit the scalar registers.
+__device__ __forceinline__ double st_vec(StBuf v, int byte, int vec)
+{
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(v, byte, vec, 0));
+}
+
+__device__ __forceinline__ void st_put(StBuf v, int byte, int vec, double x)
+{
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uvec2, x), v, byte, vec, 0);
 }
 
 // k_fused (see ppcg_fused.hpp for the steps) with rows read from the lists;
-// the diagonal is constant.
+// the diagonal is constant.  The registers stay at 61 (8 wavefronts per
+// SIMD): local copies that the compiler cannot split went to LDS, with
+// 10 us per launch.
 __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(const WorkItem *__restrict__ table,
                                                                              const int *__restrict__ count,
                                                                              const SysDesc *__restrict__ descs,
                                                                              int remap, int par)
 {
     __shared__ double lds[kFusedThreads / 64 * kNumPartials];
-    __shared__ FusedScalars sc;
+    __shared__ StScalars sc;
     const int live = *count;
     if ((int)blockIdx.x >= live)
         return;
@@ -210,18 +242,18 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
     const WorkItem wi = table[pos];
     const SysDesc &d = descs[wi.slot];
     const int R = d.frows / kFusedThreads;  // rows per thread, 1 .. kFusedRowsPerThread
-    const SysState *rin = d.frec + par;
+    // The record and the lists are the same for the workgroup or the
+    // wavefront and not written by this launch: scalar loads.
+    const __attribute__((address_space(4))) SysState *rin = as_constant((const SysState *)d.frec) + par;
     const int n = d.n;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row0 = wi.tile * d.frows;
-    const int c0 = row0 / kSellC + wave;
-    // lane k < R: the lists of this wavefront's chunk k
-    int4 ch = {0, 0, 0, 0};
-    {
-        const int c = c0 + lane * (kFusedThreads / kSellC);
-        if (lane < R && c < (n + kSellC - 1) / kSellC)
-            ch = d.schunk[c];
-    }
+    const int c0 = row0 / kSellC + wave;  // this wavefront's chunks: c0 + k * kFusedThreads / kSellC
+    const __attribute__((address_space(4))) StChunk *CH = as_constant((const StChunk *)d.schunk);
+    const bool some = c0 * kSellC < n;
+    StChunk ch = {0, 0, 0, 0};
+    if (some)
+        ch = CH[c0];
     const int nft = d.nftiles;
     const PPCG_AS1 dvec2 *PR = (const PPCG_AS1 dvec2 *)as_global(d.fpart + (size_t)par * nft * 4);
     dvec2 pa0 = {0.0, 0.0}, pb0 = {0.0, 0.0}, pa1 = {0.0, 0.0}, pb1 = {0.0, 0.0};
@@ -234,30 +266,34 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
         pa1 = PR[2 * (tid + kFusedThreads)];
         pb1 = PR[2 * (tid + kFusedThreads) + 1];
     }
+    double hist = 0.0;
+    if (tid < 2 * kStDefer)
+        hist = as_global(d.shist)[par * kStHist + tid];
     const double d0 = as_constant((const double *)d.dinv)[0];
     __asm__ volatile("" ::: "memory");  // the loads above stay above the check
     if (rin->done) {
         // publish the stop in the other slot too (see k_fused)
         if (wi.tile == 0 && threadIdx.x == 0)
-            d.frec[par ^ 1] = *rin;
+            d.frec[par ^ 1] = *(const SysState *)rin;
         return;
     }
-    double *const v0 = (double *)d.w, *const v1 = (double *)d.w1;
-    const double *gin = par ? v1 : v0;
-    double *gout = par ? v0 : v1;
-    const StBuf wb = st_buf(gin, n);
-    const PPCG_AS1 double *__restrict__ W = as_global(gin);
-    PPCG_AS1 double *__restrict__ Wo = as_global(gout);
-    PPCG_AS1 double *__restrict__ X = as_global((double *)d.x);
-    PPCG_AS1 double *__restrict__ Rv = as_global((double *)d.r);
-    PPCG_AS1 double *__restrict__ Z = as_global((double *)d.z);
-    PPCG_AS1 double *__restrict__ S = as_global((double *)d.s);
-    PPCG_AS1 double *__restrict__ P = as_global((double *)d.p);
+    // Vectors, by their byte distance from x.  w is double buffered by parity
+    // (w and u), because other tiles gather it.
+    const int vs = d.vstride;
+    const StBuf V = __builtin_amdgcn_make_buffer_rsrc(d.x, 0, 10 * vs, 0x00020000);
+    const int oW = (par ? 2 : 3) * vs, oWo = (par ? 3 : 2) * vs, oS = 8 * vs, oZ = 6 * vs, oP = 9 * vs;
+    const StBuf wb = st_buf((const double *)((const char *)d.x + oW), n);
+    // The update number i of a start.  With the ring of residuals r, q, nv, m
+    // it reads r_i from buffer i mod kStDefer and writes r_{i+1} to the next.
+    const bool ring = d.sring != 0;
+    const int at = (rin->i_start + (rin->phase ? 0 : 1)) & (ring ? kStDefer - 1 : 1);
+    static_assert(kStDefer == 4, "the ring is r, q, nv, m");
+    auto buf = [vs](int k) { return (k == 0 ? 1 : k == 1 ? 7 : k == 2 ? 5 : 4) * vs; };
+    const int oR = buf(ring ? at : 0), oRo = buf(ring ? (at + 1) & (kStDefer - 1) : 0);
     // 0. This thread's first row of n = A m.
-    double nv0 = 0.0;
-    if (c0 * kSellC < n)  // uniform per wavefront
-        nv0 = st_row(d, __builtin_amdgcn_readlane(ch.x, 0), __builtin_amdgcn_readlane(ch.y, 0),
-                     __builtin_amdgcn_readlane(ch.z, 0), wb, (row0 + tid) * 8, d0);
+    double nv = 0.0;
+    if (some)
+        nv = st_row(d, ch, wb, (row0 + tid) * 8, d0);
     // 1. The previous launch's partials and the scalar recurrences.
     {
         double v[kNumPartials] = {0.0, 0.0, 0.0, 0.0};
@@ -280,22 +316,15 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
             v[2] = v[2] + b[0];
             v[3] = v[3] + b[1];
         }
+        if (tid < 2 * kStDefer)
+            sc.hist[tid] = hist;
         block_sum<kFusedThreads, kNumPartials>(v, lds);
         if (tid == 0) {
-            SysState loc = *rin;
-            if (!loc.phase) {
-                loc.alpha_x = loc.alpha;
-                loc.x_pending ^= 1;
-            }
+            SysState loc = *(const SysState *)rin;
             scalar_update<kNumPartials>(d, &loc, v);
             sc.alpha = loc.alpha;
             sc.beta = loc.beta;
-            sc.alpha_x = loc.alpha_x;
-            sc.x_pending = loc.x_pending;
             sc.go = !loc.done;
-            sc.x_finish = loc.done && loc.x_pending;
-            if (sc.x_finish)
-                loc.x_pending = 0;
             if (wi.tile == 0) {
                 d.frec[par ^ 1] = loc;
                 *d.st = loc;
@@ -304,52 +333,81 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
         __syncthreads();
     }
     if (!sc.go) {
-        if (sc.x_finish) {
-            const double a = sc.alpha_x;
+        // the updates of x (with the ring, of p and x) deferred so far, so
+        // that x is complete when the host reads the state
+        if (at > 0)
             for (int k = 0; k < R; ++k) {
                 const int i = row0 + k * kFusedThreads + tid;
-                if (i < n)
-                    X[i] = X[i] + a * P[i];
+                if (i < n) {
+                    double p = st_vec(V, i * 8, oP), x = st_vec(V, i * 8, 0);
+#pragma unroll
+                    for (int t = 0; t < kStDefer - 1; ++t)
+                        if (t < at) {
+                            if (ring)
+                                p = d0 * st_vec(V, i * 8, buf(t)) + sc.hist[kStDefer + t] * p;
+                            x = x + sc.hist[t] * p;
+                        }
+                    st_put(V, i * 8, 0, x);
+                }
             }
-        }
         return;
     }
+    const double sa = sc.alpha, sb = sc.beta;
+    if (wi.tile == 0 && tid < 2 * kStDefer)
+        as_global(d.shist)[(par ^ 1) * kStHist + tid] =
+            (tid & (kStDefer - 1)) != at ? hist : tid < kStDefer ? sa : sb;
     // 2. Per row of this thread: n = A m into a register, then the update.
-    const double sa = sc.alpha, sb = sc.beta, ax = sc.alpha_x;
-    const bool xp = sc.x_pending != 0;
+    const bool full = at == (ring ? kStDefer - 1 : 1);
     double acc[kNumPartials] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
     for (int k = 0; k < R; ++k) {
         const int i = row0 + k * kFusedThreads + tid;
         if (row0 + k * kFusedThreads + wave * kSellC >= n)
             break;  // uniform per wavefront
-        double z = 0.0, w = 0.0, s = 0.0, p = 0.0, r = 0.0, xo = 0.0;
-        if (i < n) {
-            z = Z[i];
-            w = W[i];
-            s = S[i];
-            p = P[i];
-            r = Rv[i];
-            if (xp)
-                xo = X[i];
+        // a lane past the last row reads zeros and its stores are dropped
+        const int ib = i < n ? i * 8 : 0x7ffffff0;
+        double w = st_load(wb, ib), s = st_vec(V, ib, oS), z = st_vec(V, ib, oZ), r = st_vec(V, ib, oR);
+        if (k > 0) {
+            ch = CH[c0 + k * (kFusedThreads / kSellC)];
+            nv = st_row(d, ch, wb, i * 8, d0);
         }
-        const double nv = k == 0 ? nv0
-                                 : st_row(d, __builtin_amdgcn_readlane(ch.x, k), __builtin_amdgcn_readlane(ch.y, k),
-                                          __builtin_amdgcn_readlane(ch.z, k), wb, i * 8, d0);
-        if (i < n) {
-            const double pold = p;
-            double u, mo;
-            vma_elem<double, kNumPartials>(sa, sb, nv, z, w, s, p, r, d0, u, mo, acc);
-            Z[i] = z;
-            S[i] = s;
-            P[i] = p;
-            Rv[i] = r;
-            Wo[i] = w;
-            if (xp) {
-                const double x1 = xo + ax * pold;
-                X[i] = x1 + sa * p;
+        if (ring) {
+            if (full) {
+                double p = st_vec(V, ib, oP), x = st_vec(V, ib, 0), q[kStDefer];
+#pragma unroll
+                for (int t = 0; t < kStDefer - 1; ++t)
+                    q[t] = st_vec(V, ib, buf(t));
+#pragma unroll
+                for (int t = 0; t < kStDefer - 1; ++t) {
+                    p = d0 * q[t] + sc.hist[kStDefer + t] * p;
+                    x = x + sc.hist[t] * p;
+                }
+                p = d0 * r + sb * p;
+                x = x + sa * p;
+                st_put(V, ib, oP, p);
+                st_put(V, ib, 0, x);
+            }
+        } else {
+            const double pold = st_vec(V, ib, oP), p = d0 * r + sb * pold;
+            st_put(V, ib, oP, p);
+            if (full) {
+                const double x = st_vec(V, ib, 0) + sc.hist[0] * pold;
+                st_put(V, ib, 0, x + sa * p);
             }
         }
+        z = nv + sb * z;
+        s = w + sb * s;
+        r = r - sa * s;
+        w = w - sa * z;
+        const double u = d0 * r;
+        acc[0] = acc[0] + r * u;
+        acc[1] = acc[1] + w * u;
+        acc[2] = acc[2] + u * u;
+        acc[3] = acc[3] + r * r;
+        st_put(V, ib, oS, s);
+        st_put(V, ib, oRo, r);
+        st_put(V, ib, oWo, w);
+        st_put(V, ib, oZ, z);
     }
     block_sum<kFusedThreads, kNumPartials>(acc, lds);
     if (tid == 0) {
