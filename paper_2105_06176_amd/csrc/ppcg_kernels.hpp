@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "ppcg_internal.hpp"
+#include "ppcg_lists.hpp"
 
 namespace ppcg {
 
@@ -651,12 +652,6 @@ __device__ __forceinline__ void sell_row_straight(const int64_t *__restrict__ cp
 // read through the constant address space, so that the uniform loads become
 // scalar loads (the few distinct lists stay in the scalar cache) and the
 // gathers wait on no vector load.
-template <typename T>
-__device__ __forceinline__ const __attribute__((address_space(4))) T *as_constant(const T *p)
-{
-    return (const __attribute__((address_space(4))) T *)p;
-}
-
 // Entries k0 .. k0 + L - 1 of a row stored on its chunk's shared offset list
 // `po`: the column of entry j is row + po[k0 + j], clamped into [0, last]
 // (an entry the row lacks is a zero value, at a column that may lie past the
@@ -1281,6 +1276,26 @@ __device__ __forceinline__ void spmv_tile(const SysDesc &d, const VT *__restrict
     }
 }
 
+// spmv_tile on chunk lists (FP64 vectors, one input).
+template <typename T, int MODE>
+__device__ __forceinline__ void spmv_tile_lists(const SysDesc &d, const WorkItem wi, double (&acc)[kReplPartials])
+{
+    if constexpr (std::is_same<T, double>::value && SpmvIn<MODE>::NX == 1) {
+        const T *xin[1];
+        spmv_inputs<T, MODE>(d, xin);
+        const int chunk = wi.tile * kSellChunksPerTile + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const int i = chunk * kSellC + (threadIdx.x & 63);
+        if (chunk * kSellC < d.n) {
+            T y[1] = {0.0};
+            if constexpr (MODE != MODE_INIT0)
+                y[0] = st_row<false>(d, as_constant((const StChunk *)d.schunk)[chunk], st_buf(xin[0], d.n), i * 8,
+                                     0.0);
+            if (i < d.n)
+                spmv_epilogue<T, MODE>(d, i, y, acc);
+        }
+    }
+}
+
 // Eight waves per SIMD (at most 64 VGPRs): the gathers depend on the column
 // loads, so latency is hidden by the number of waves in flight.
 template <typename T, int MODE>
@@ -1304,6 +1319,8 @@ __global__ __launch_bounds__(kSpmvThreads, PPCG_SPMV_WAVES) void k_spmv(const Wo
     double acc[kReplPartials] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     if (!kTrueOperator<MODE> && d.vals32) {
         spmv_tile<float, T, MODE>(d, d.val32, wi, acc);
+    } else if (std::is_same<T, double>::value && SpmvIn<MODE>::NX == 1 && d.schunk) {
+        spmv_tile_lists<T, MODE>(d, wi, acc);
     } else if (std::is_same<T, double>::value && SpmvIn<MODE>::NX == 1 && d.vidx && d.fmt == FMT_SELL) {
         // the value table, once per workgroup (one work item: uniform); the
         // two-vector SpMVs of the reliable updates read the values

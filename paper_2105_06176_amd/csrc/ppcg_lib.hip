@@ -940,6 +940,9 @@ static ppcg_status tune_vtab(ppcg_handle *h, const double *val_host, const doubl
     const unsigned fl = h->opt.flags;
     if (!PPCG_SELL_VTAB || h->fmt != FMT_SELL || (fl & PPCG_FLAG_SELL_FULL_VALUES))
         return PPCG_OK;
+    // chunk lists leave nothing that reads the table
+    if (h->schunk && !(fl & PPCG_FLAG_SELL_VALUE_TABLE))
+        return PPCG_OK;
     const std::pair<int, int> sig((int)std::log2((double)h->n), (int)std::lround((double)h->nnz_stored / h->n));
     bool known = false, kept = false;
     if (!(fl & PPCG_FLAG_SELL_VALUE_TABLE)) {
@@ -1049,18 +1052,18 @@ static void shared_for_fused(ppcg_handle *h)
 
 // Describe the chunks by lists alone (ppcg_stencil.hpp) when every one
 // qualifies: rows in their own order on shared offset lists, one value per
-// list entry, a constant diagonal, the value table kept and neither a column
-// layout nor the two-launch form pinned.  The distinct lists may take at most
+// list entry, a constant diagonal, and no column layout, 8-byte values or the
+// two-launch form pinned.  The distinct lists may take at most
 // half the bytes of the one-byte value indices that the lists replace
 // (or 64 KiB): a wavefront reads them through the scalar cache, and matrices
 // whose chunks are mostly of different kinds gain nothing.
 static ppcg_status build_stencil(ppcg_handle *h)
 {
     const unsigned fl = h->opt.flags;
-    if (h->fmt != FMT_SELL || !h->cpat || h->perm || !h->vidx || !h->dinv_const || h->n > kStMaxRows ||
+    if (h->fmt != FMT_SELL || !h->cpat || h->perm || !h->dinv_const || h->n > kStMaxRows ||
         (h->n <= PPCG_SMALL_MAX_ROWS && !(fl & PPCG_FLAG_ITER_FUSED)) ||
         (fl & (PPCG_FLAG_SELL_COL16 | PPCG_FLAG_SELL_COL32 | PPCG_FLAG_SELL_NO_SHARED_OFFSETS |
-               PPCG_FLAG_ITER_TWO_LAUNCH)) != 0)
+               PPCG_FLAG_SELL_FULL_VALUES | PPCG_FLAG_ITER_TWO_LAUNCH)) != 0)
         return PPCG_OK;
     hipStream_t s = h->stream;
     const int nc = h->nchunks;
@@ -2947,8 +2950,8 @@ ppcg_status ppcg_create(const ppcg_csr *A, const ppcg_options *opt, void *hip_st
     }
     CKS(alloc_f64_vectors(h));
     CKS(choose_format(h, rp, ci, val, rowlen, dinv_orig, rowlen_h));
-    CKS(tune_vtab(h, A->mem == PPCG_MEM_HOST ? A->values : nullptr, val));
     CKS(build_stencil(h));
+    CKS(tune_vtab(h, A->mem == PPCG_MEM_HOST ? A->values : nullptr, val));
     CKS(tune_shared(h));
     CKS(tune_form(h));
     shared_for_fused(h);
@@ -3165,7 +3168,7 @@ ppcg_status ppcg_get_matrix_info(const ppcg_handle *h, ppcg_matrix_info *mi)
     mi->diag_const = h->dinv_const ? 1 : 0;
     const bool pcg = h->opt.method == PPCG_METHOD_PCG || h->opt.precision == PPCG_MIXED_FP32;
     mi->value_bytes = h->opt.precision == PPCG_MIXED_FP32 || h->opt.precision == PPCG_MIXED_FP32_VALUES ? 4
-                      : (h->vidx && !pcg)                                                              ? 1
+                      : ((h->vidx || h->schunk) && !pcg)                                                              ? 1
                                                                                                        : 8;
     mi->distinct_values = h->nvtab;
     mi->iter_launches = (h->form == FORM_FUSED && !pcg && h->opt.precision == PPCG_FP64) ? 1 : 2;

@@ -37,9 +37,6 @@
 
 namespace ppcg {
 
-// Largest system: the byte offsets of ten vectors fit 31 bits.
-constexpr int kStMaxRows = 25000000;
-
 // ---------------------------------------------------------------- setup
 __device__ __forceinline__ unsigned long long st_mix(unsigned long long h, unsigned long long v)
 {
@@ -137,74 +134,7 @@ __global__ __launch_bounds__(64) void k_st_verify(int nchunks, const int64_t *__
         atomicOr(flag, 1u);
 }
 
-// ---------------------------------------------------------------- rows
-typedef unsigned uvec2 __attribute__((ext_vector_type(2)));
-typedef __amdgpu_buffer_rsrc_t StBuf;
-
-// Raw buffer over n doubles: a load whose 8 bytes are not inside returns 0.
-__device__ __forceinline__ StBuf st_buf(const double *p, int n)
-{
-    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, n * 8, 0x00020000);
-}
-
-__device__ __forceinline__ double st_load(StBuf b, int byte)
-{
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, byte, 0, 0));
-}
-
-// A chunk's list start, mask start and length.
-typedef int StChunk __attribute__((ext_vector_type(4)));
-
-// One chunk's lists (uniform over the wavefront).
-struct StLists {
-    const __attribute__((address_space(4))) int *off;
-    const __attribute__((address_space(4))) double *val;
-    const __attribute__((address_space(4))) unsigned long long *mask;
-};
-
-// Entries k0 .. k0 + L - 1 of a row: the gathers back to back, then their
-// products added in entry order; each is value * (d0 * w[col]), m = M^-1 w
-// formed from the gathered w as everywhere in the single-launch form.
-template <int L>
-__device__ __forceinline__ double st_span(const StLists p, int k0, StBuf w, int rowb, double d0, double a)
-{
-    double x[L];
-#pragma unroll
-    for (int j = 0; j < L; ++j)
-        x[j] = st_load(w, rowb + p.off[k0 + j]);
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-        const bool has = __builtin_amdgcn_inverse_ballot_w64(p.mask[k0 + j]);
-        a = a + p.val[k0 + j] * (d0 * (has ? x[j] : 0.0));
-    }
-    return a;
-}
-
-template <int M>
-__device__ __forceinline__ double st_tail(int rem, const StLists p, int k0, StBuf w, int rowb, double d0, double a)
-{
-    if constexpr (M > 0) {
-        if (rem == M)
-            return st_span<M>(p, k0, w, rowb, d0, a);
-        return st_tail<M - 1>(rem, p, k0, w, rowb, d0, a);
-    } else {
-        return a;
-    }
-}
-
-// (A m)[row] of one lane's row of chunk ch.
-__device__ __forceinline__ double st_row(const SysDesc &d, StChunk ch, StBuf w, int rowb, double d0)
-{
-    constexpr int B = 8;
-    const int len = ch[2];
-    const StLists p{as_constant(d.soff) + ch[0], as_constant(d.sval) + ch[0], as_constant(d.smask) + ch[1]};
-    double a = 0.0;
-    int k0 = 0;
-    for (; k0 + B <= len; k0 += B)
-        a = st_span<B>(p, k0, w, rowb, d0, a);
-    return st_tail<B - 1>(len - k0, p, k0, w, rowb, d0, a);
-}
-
+// ---------------------------------------------------------------- iteration
 struct StScalars {
     double alpha, beta;
     double hist[2 * kStDefer];  // alpha, beta of the updates since the last full ring
@@ -293,7 +223,7 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
     // 0. This thread's first row of n = A m.
     double nv = 0.0;
     if (some)
-        nv = st_row(d, ch, wb, (row0 + tid) * 8, d0);
+        nv = st_row<true>(d, ch, wb, (row0 + tid) * 8, d0);
     // 1. The previous launch's partials and the scalar recurrences.
     {
         double v[kNumPartials] = {0.0, 0.0, 0.0, 0.0};
@@ -369,7 +299,7 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
         double w = st_load(wb, ib), s = st_vec(V, ib, oS), z = st_vec(V, ib, oZ), r = st_vec(V, ib, oR);
         if (k > 0) {
             ch = CH[c0 + k * (kFusedThreads / kSellC)];
-            nv = st_row(d, ch, wb, i * 8, d0);
+            nv = st_row<true>(d, ch, wb, i * 8, d0);
         }
         if (ring) {
             if (full) {

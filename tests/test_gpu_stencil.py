@@ -104,6 +104,24 @@ def test_lists_equal_columns_and_oracle(name):
         s.close()
 
 
+@pytest.mark.parametrize("name", ["poisson2d_67", "lines_of_63", "poisson125_40", "halves_inside_a_chunk"])
+def test_spmv_and_initial_guess_on_lists(name):
+    """The SpMV, the initialisation from a guess and the true residual read the lists too (no value table is built):
+    bit for bit the oracle's product and the per-entry columns' solve."""
+    gen, k, _ = CASES[name]
+    A = gen()
+    b = rhs_from_solution(A, xstar_uniform(A.n, 3))
+    x0 = xstar_uniform(A.n, 8)
+    S = Solver(A, fixed_iters=k, spmv_format="sell", flags=ppcg.FLAG_ITER_FUSED | ppcg.FLAG_SELL_SHARED_OFFSETS)
+    N = Solver(A, fixed_iters=k, spmv_format="sell", flags=COLUMNS)
+    assert np.array_equal(host(S.spmv(dev(x0))), oracle.spmv(A, x0))
+    x, info = S.solve(dev(b), x0=dev(x0))
+    y, other = N.solve(dev(b), x0=dev(x0))
+    assert np.array_equal(host(x), host(y)) and info["rel_resid_true"] == other["rel_resid_true"]
+    for s in (S, N):
+        s.close()
+
+
 def test_batch_of_list_and_column_systems_equals_solo_bitwise():
     """Both kernels in one batch, twice (captured graphs replayed), with systems that end at different times."""
     mats = [poisson2d(80), shifted(poisson2d(121), 0.3), poisson3d(33), box(31, 17, 20), poisson2d(40)]
