@@ -133,6 +133,7 @@ struct ppcg_handle {
     ppcg::PrecData f64, f32;
     double *part = nullptr;   // 2 x ntiles x 4 partial sums (shared by both precisions)
     double *part32 = nullptr; // partials of the FP32-vector sequence
+    ppcg::SysState *prs = nullptr, *prs32 = nullptr;  // classic PCG's scalar records, 2 each
     double setup_ms = 0.0;
     ppcg::Engine *solo = nullptr;  // cached single-system engine
     ppcg::BatchCtx *batch = nullptr;  // cached engine of batches led by this handle
@@ -216,7 +217,7 @@ enum JobStage {
 // Per-precision set of system slots, work table and captured graph.
 struct Group {
     int prec = PREC_F64;
-    bool pcg = false;               // iterates Algorithm 1 (two launches per iteration, PAR alternating)
+    bool pcg = false;               // iterates Algorithm 1, two launches per iteration (work items are fused tiles)
     bool fused = false;             // FP64 PIPECG, one launch per iteration (work items are fused tiles)
     bool stencil = false;           // ... of k_stencil instead of k_fused
     int cap_sys = 0;

@@ -56,10 +56,14 @@ constexpr int kFusedResidentPerCU = 3;
 // 128^3 (2,097,152 rows) R = 8 (512 tiles) 51.9 against R = 4 55.0 and
 // R = 6 56.1; 2048^2 (4,194,304 rows) R = 16 (512 tiles) 91.4 against R = 4
 // 95.6 and R = 8 101.3; 160^3 7-point R = 16 94.1 against R = 4 98.0.
+// Classic PCG's launches hold kPcgResidentPerCU workgroups (at most 64 VGPRs);
+// ms per solve with R = 2, 3, 4, 8: 27-point 128^3 in FP32 47.7, 48.0, 46.0,
+// 46.5 (taken: 4), 953,025 rows 7-point 5.78, 5.90, 5.79, 6.31 (taken: 4).
+constexpr int kPcgResidentPerCU = 4;
 #ifndef PPCG_FUSED_TILE_TARGET
 #define PPCG_FUSED_TILE_TARGET 256
 #endif
-inline int fused_tile_rows(int n, int cus)
+inline int fused_tile_rows(int n, int cus, int resident = kFusedResidentPerCU)
 {
     constexpr int kTarget = PPCG_FUSED_TILE_TARGET;
     int r0 = (n + kTarget * kFusedThreads - 1) / (kTarget * kFusedThreads);
@@ -72,9 +76,7 @@ inline int fused_tile_rows(int n, int cus)
         const long long rows = (long long)r * kFusedThreads;
         const long long tiles = (n + rows - 1) / rows;
         const long long w = (tiles + cus - 1) / cus;
-        const long long cost = w <= kFusedResidentPerCU
-                                   ? r * w
-                                   : r * kFusedResidentPerCU * ((w + kFusedResidentPerCU - 1) / kFusedResidentPerCU);
+        const long long cost = w <= resident ? r * w : r * resident * ((w + resident - 1) / resident);
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost;
             best = r;
@@ -264,6 +266,7 @@ struct SysDesc {
     const void *b;        // right-hand side (internal copy)
     double *part;         // partial sums: 2 slots x ntiles x kPartStride
     SysState *st;
+    SysState *prs;        // classic PCG: the two scalar records of an iteration
     // single-launch iteration (ppcg_fused.hpp); unused by the two-launch form
     int nftiles;          // fused tiles (of frows rows)
     int frows;            // rows per fused tile (fused_tile_rows(n, compute units))

@@ -168,6 +168,9 @@ static ByteModel byte_model(const ppcg_handle *h, int prec)
     const bool sh = h->shared_on;
     const double ie = sh ? 0.0 : (h->col16 && (PPCG_PCG_V32_COL16 || !(pcg && prec == PREC_V32))) ? 2.0 : 4.0;
     bm.spmv = (me + ie) * (double)h->nnz + ptr + (sh ? 4.0 * h->nchunks : 0.0) + (pcg ? 4.0 : 2.0) * ve * n;
+    // classic PCG on chunk lists: 16 bytes per chunk stand for the matrix
+    if (h->schunk && pcg)
+        bm.spmv = 16.0 * h->nchunks + 4.0 * ve * n;
     // the single-launch form keeps n in registers (neither written by the
     // SpMV nor read by the update) and, with a constant diagonal, forms
     // m = M^-1 w in the next launch's gathers instead of writing it (the
@@ -486,7 +489,7 @@ ppcg_status fill_desc(ppcg_handle *h, int prec, SysState *st, SysDesc *d, double
     d->nvtab = h->nvtab;
     d->cpat = h->shared_on ? h->cpat : nullptr;
     d->pats = h->pats;
-    if (prec == PREC_F64 && h->form == FORM_FUSED) {
+    if (h->form == FORM_FUSED) {
         d->schunk = h->schunk;
         d->soff = h->soff;
         d->sval = h->sval;
@@ -516,6 +519,7 @@ ppcg_status fill_desc(ppcg_handle *h, int prec, SysState *st, SysDesc *d, double
     d->p = pd.vec[VP];
     d->b = pd.vec[VB];
     d->part = prec == PREC_F64 ? h->part : h->part32;
+    d->prs = prec == PREC_F64 ? h->prs : h->prs32;
     d->st = st;
     d->frows = fused_tile_rows(h->n, h->cus);
     d->nftiles = (h->n + d->frows - 1) / d->frows;
@@ -523,6 +527,19 @@ ppcg_status fill_desc(ppcg_handle *h, int prec, SysState *st, SysDesc *d, double
     d->fpart = h->fpart;
     d->w1 = h->w1;
     return PPCG_OK;
+}
+
+// Tiles of classic PCG's launches over a handle's system.
+static int pcg_tiles(const ppcg_handle *h)
+{
+    const int fr = fused_tile_rows(h->n, h->cus, kPcgResidentPerCU);
+    return (h->n + fr - 1) / fr;
+}
+
+static void set_pcg_tiles(const ppcg_handle *h, SysDesc *d)
+{
+    d->frows = fused_tile_rows(h->n, h->cus, kPcgResidentPerCU);
+    d->nftiles = pcg_tiles(h);
 }
 
 int fused_tiles(const ppcg_handle *h)
@@ -554,11 +571,11 @@ static ppcg_status plain_setup(ppcg_handle *h, double tol, int fixed, int maxit)
         PPCG_HIP(hipMalloc(&h->plain_desc, sizeof(SysDesc)));
         PPCG_HIP(hipMalloc(&h->plain_st, sizeof(SysState)));
         PPCG_HIP(hipMalloc(&h->plain_tab, sizeof(WorkItem) * h->ntiles));
-        PPCG_HIP(hipMalloc(&h->plain_cnt, sizeof(int) * 2));  // [1]: fused tiles
+        PPCG_HIP(hipMalloc(&h->plain_cnt, sizeof(int) * 3));  // [1]: fused tiles, [2]: classic PCG's
         std::vector<WorkItem> th(h->ntiles);
         for (int t = 0; t < h->ntiles; ++t)
             th[t] = {0, t};
-        const int count[2] = {h->ntiles, fused_tiles(h)};
+        const int count[3] = {h->ntiles, fused_tiles(h), pcg_tiles(h)};
         PPCG_HIP(hipMemcpyAsync(h->plain_tab, th.data(), sizeof(WorkItem) * count[0], hipMemcpyHostToDevice, s));
         PPCG_HIP(hipMemcpyAsync(h->plain_cnt, count, sizeof count, hipMemcpyHostToDevice, s));
         PPCG_HIP(hipStreamSynchronize(s));  // host sources are about to go out of scope
@@ -1482,10 +1499,11 @@ static ppcg_status alloc_f64_vectors(ppcg_handle *h)
     const size_t n = (size_t)h->n;
     const size_t vb = aligned(n * sizeof(double) + kVecPad);
     const size_t pb = aligned((size_t)2 * h->ntiles * kPartStride * sizeof(double));
-    PPCG_TRY(h->f64.arena.alloc(11 * vb + pb + 2 * 256));
+    PPCG_TRY(h->f64.arena.alloc(11 * vb + pb + 2 * sizeof(SysState) + 3 * 256));
     for (int k = 0; k < 11; ++k)
         h->f64.vec[k] = h->f64.arena.take(n * sizeof(double) + kVecPad);
     h->part = (double *)h->f64.arena.take((size_t)2 * h->ntiles * kPartStride * sizeof(double));
+    h->prs = (SysState *)h->f64.arena.take(2 * sizeof(SysState));
     return PPCG_OK;
 }
 
@@ -1513,13 +1531,14 @@ ppcg_status ensure_f32(ppcg_handle *h)
     const size_t vb = aligned(n * sizeof(float));
     const size_t pb = aligned((size_t)2 * h->ntiles * kPartStride * sizeof(double));
     PrecData &pd = h->f32;
-    PPCG_TRY(pd.arena.alloc(12 * vb + pb + 4 * 256));
+    PPCG_TRY(pd.arena.alloc(12 * vb + pb + 2 * sizeof(SysState) + 5 * 256));
     pd.prec = PREC_F32;
     pd.val = h->val32;
     pd.dinv = pd.arena.take(n * sizeof(float));
     for (int k = 0; k < 11; ++k)
         pd.vec[k] = pd.arena.take(n * sizeof(float));
     h->part32 = (double *)pd.arena.take((size_t)2 * h->ntiles * kPartStride * sizeof(double));
+    h->prs32 = (SysState *)pd.arena.take(2 * sizeof(SysState));
     k_convert<float, double><<<blocks_for(n, 256), 256, 0, h->stream>>>(n, h->dinv64, (float *)pd.dinv);
     PPCG_HIP(hipGetLastError());
     PPCG_HIP(hipStreamSynchronize(h->stream));
@@ -1802,29 +1821,33 @@ void set_csr_error(const unsigned (&err)[2])
     set_error("bad CSR: %s (first row %u)", what.c_str(), err[1]);
 }
 
-// One iteration of a group: the fused update, then the SpMV with the
-// in-launch reduction.  The FP32-values group uses the fused-update variant
-// that also emits the direct-denominator partials.
-static void launch_iter_pair(hipStream_t s, const Group &g, int grid, int remap)
+// iters iterations of a group over its table.  The FP32-values group uses
+// the fused-update variant that also emits the direct-denominator partials.
+static void launch_iters(hipStream_t s, const Group &g, int grid, int remap, int iters)
 {
     if (g.pcg) {
-        // Algorithm 1: SpMV, alpha, vector updates, stopping test and beta.
-        const int sg = std::max(g.g_sys_grid, 1);
-        if (g.prec == PREC_F32)
-            k_pcg_spmv<float><<<grid, kSpmvThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, PPCG_XCD_REMAP_SPMV);
-        else
-            k_pcg_spmv<double><<<grid, kSpmvThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, PPCG_XCD_REMAP_SPMV);
-        k_pcg_alpha<<<sg, kPcgRedThreads, 0, s>>>(g.sys_d, g.sys_count_d, g.desc_d);
-        if (g.prec == PREC_F32)
-            k_pcg_vma<float><<<grid, kVmaThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, remap);
-        else
-            k_pcg_vma<double><<<grid, kVmaThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, remap);
-        k_pcg_update<PCG_ITER><<<sg, kPcgRedThreads, 0, s>>>(g.sys_d, g.sys_count_d, g.desc_d);
-    } else if (g.prec == PREC_V32) {
-        k_vma<double, true><<<grid, kVmaThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, remap);
-        k_spmv<double, MODE_ITER><<<grid, kSpmvThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, PPCG_XCD_REMAP_SPMV);
-    } else {
-        launch_pipecg_iter(s, g.table_d, g.count_d, g.desc_d, grid, remap);
+        // Algorithm 1: SpMV with the stopping test and beta, vector updates with alpha.
+        for (int i = 0; i < iters; ++i) {
+            if (g.prec == PREC_F32) {
+                k_pcg_spmv<float><<<grid, kSpmvThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, remap, i == 0);
+                k_pcg_vma<float><<<grid, kPcgVmaThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, remap);
+            } else {
+                k_pcg_spmv<double><<<grid, kSpmvThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, remap, i == 0);
+                k_pcg_vma<double><<<grid, kPcgVmaThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, remap);
+            }
+        }
+        k_pcg_update<PCG_ITER><<<std::max(g.g_sys_grid, 1), kPcgRedThreads, 0, s>>>(g.sys_d, g.sys_count_d,
+                                                                                     g.desc_d);
+        return;
+    }
+    for (int i = 0; i < iters; ++i) {
+        if (g.prec == PREC_V32) {
+            k_vma<double, true><<<grid, kVmaThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d, remap);
+            k_spmv<double, MODE_ITER><<<grid, kSpmvThreads, 0, s>>>(g.table_d, g.count_d, g.desc_d,
+                                                                   PPCG_XCD_REMAP_SPMV);
+        } else {
+            launch_pipecg_iter(s, g.table_d, g.count_d, g.desc_d, grid, remap);
+        }
     }
 }
 
@@ -1900,8 +1923,7 @@ ppcg_status Engine::ensure_graph(Group &g, int iters, hipGraphExec_t *exec)
     if (g.fused)
         launch_fused_chunk(stream_, g.table_d, g.count_d, g.desc_d, grid, iters, g.stencil);
     else
-        for (int i = 0; i < iters; ++i)
-            launch_iter_pair(stream_, g, grid, remap);
+        launch_iters(stream_, g, grid, remap, iters);
     hipError_t e = hipStreamEndCapture(stream_, &cg.graph);
     if (e != hipSuccess) {
         set_error("hipStreamEndCapture failed: %s", hipGetErrorString(e));
@@ -2145,6 +2167,7 @@ ppcg_status Engine::add(ppcg_handle *h, int mixed, double tol, const double *, i
             g.slot_used[slot] = 0;
             return rc;
         }
+        set_pcg_tiles(h, &g.desc_h[slot]);
         if (v32)
             g.desc_h[slot].repl_factor = o.inner_tol > 0 ? o.inner_tol : 1e-3;
         PPCG_TRY(upload_desc(g, slot));
@@ -2227,6 +2250,7 @@ ppcg_status Engine::add(ppcg_handle *h, int mixed, double tol, const double *, i
             rc = fill_desc(h, PREC_F32, gi.st_d + j.slot32, &gi.desc_h[j.slot32], tol, 0, o.max_iter, STOP_REL);
             if (rc != PPCG_OK)
                 return fail(rc);
+            set_pcg_tiles(h, &gi.desc_h[j.slot32]);
             gi.desc_h[j.slot32].repl_factor = o.inner_tol > 0 ? o.inner_tol : kPcgMixReplFactor;
             gi.desc_h[j.slot32].pair = j.slot64;
             g64_.desc_h[j.slot64].pair = j.slot32;
@@ -2437,7 +2461,7 @@ ppcg_status Engine::step(int graph_iters)
             if (j.finished || j.stage != JS_ITER || &pgroup(j) != g)
                 continue;
             const int sl = pslot(j);
-            const int nt = g == &gs_ ? 1 : g->fused ? g->desc_h[sl].nftiles : g->desc_h[sl].ntiles;
+            const int nt = g == &gs_ ? 1 : g->fused || g->pcg ? g->desc_h[sl].nftiles : g->desc_h[sl].ntiles;
             for (int t = 0; t < nt; ++t)
                 items.push_back({sl, t});
         }
@@ -3255,6 +3279,15 @@ ppcg_status ppcg_time_kernels(ppcg_handle *h, const double *b, int32_t iters, do
         clean();
         return PPCG_OK;
     }
+    SysDesc dp;  // classic PCG: its own tiles
+    int pgrid = 0;
+    if (pcg) {
+        PPCG_TRY(fill_desc(h, PREC_F64, h->plain_st, &dp, 0.0, INT_MAX, INT_MAX, STOP_REL));
+        set_pcg_tiles(h, &dp);
+        pgrid = dp.nftiles;
+        PPCG_HIP_CLEAN(hipMemcpyAsync(h->plain_desc, &dp, sizeof dp, hipMemcpyHostToDevice, s), clean());
+        PPCG_HIP_CLEAN(hipStreamSynchronize(s), clean());
+    }
     k_spmv<double, MODE_INIT1><<<grid, kSpmvThreads, 0, s>>>(tab, cnt, dd, PPCG_XCD_REMAP_SPMV);
     if (pcg) {
         k_pcg_dots<double><<<grid, kVmaThreads, 0, s>>>(tab, cnt, dd);
@@ -3270,14 +3303,10 @@ ppcg_status ppcg_time_kernels(ppcg_handle *h, const double *b, int32_t iters, do
     for (int i = 0; i < iters; ++i) {
         const int rv = (int)PPCG_XCD_REMAP, rs = (int)PPCG_XCD_REMAP_SPMV;
         if (pcg) {
-            // the two streaming kernels are timed; the per-system reductions
-            // between them run untimed
-            hipExtLaunchKernelGGL(k_pcg_spmv<double>, dim3(grid), dim3(kSpmvThreads), 0, s, ev[4 * i + 2], ev[4 * i + 3], 0,
-                                  tab, cnt, dd, rs);
-            k_pcg_alpha<<<1, kPcgRedThreads, 0, s>>>(tab, cnt, dd);
-            hipExtLaunchKernelGGL(k_pcg_vma<double>, dim3(grid), dim3(kVmaThreads), 0, s, ev[4 * i], ev[4 * i + 1], 0, tab,
-                                  cnt, dd, rv);
-            k_pcg_update<PCG_ITER><<<1, kPcgRedThreads, 0, s>>>(tab, cnt, dd);
+            hipExtLaunchKernelGGL(k_pcg_spmv<double>, dim3(pgrid), dim3(kSpmvThreads), 0, s, ev[4 * i + 2],
+                                  ev[4 * i + 3], 0, tab, cnt + 2, dd, rv, i == 0 ? 1 : 0);
+            hipExtLaunchKernelGGL(k_pcg_vma<double>, dim3(pgrid), dim3(kPcgVmaThreads), 0, s, ev[4 * i],
+                                  ev[4 * i + 1], 0, tab, cnt + 2, dd, rv);
         } else {
             hipExtLaunchKernelGGL(k_vma<double>, dim3(grid), dim3(kVmaThreads), 0, s, ev[4 * i], ev[4 * i + 1], 0,
                                   tab, cnt, dd, rv);

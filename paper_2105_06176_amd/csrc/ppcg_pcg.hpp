@@ -2,22 +2,37 @@
 // III-A) on the device, for comparison with the pipelined method, and as the
 // iteration of the FP32-values mode when selected.
 //
-// One iteration is four launches:
+// One iteration is two launches over tiles of frows rows (as the single-launch
+// form of Algorithm 2, fused_tile_rows):
 //
-//   k_pcg_spmv      (per tile)   p = u + beta p, formed on the fly for every
-//                                gathered entry and written for the tile's
-//                                own rows into the other buffer of a
-//                                double-buffered pair; s = A p; partial sums
-//                                of (s, p).
-//   k_pcg_alpha     (per system) reduce (s, p) in a fixed order; alpha.
-//   k_pcg_vma       (per tile)   x += alpha p, r -= alpha s, u = M^-1 r;
-//                                partial sums of (u, r), (u, u), (r, r).
-//   k_pcg_update    (per system) reduce them; stopping test; beta.
+//   k_pcg_spmv   every workgroup reduces the partial sums of (u, r), (u, u),
+//                (r, r) that the previous k_pcg_vma wrote and runs the
+//                stopping test and beta itself; p = u + beta p, formed on the
+//                fly for every gathered entry and written for the tile's own
+//                rows into the other buffer of a double-buffered pair;
+//                s = A p; partial sums of (s, p).
+//   k_pcg_vma    every workgroup reduces (s, p) and forms alpha; x += alpha p,
+//                r -= alpha s, u = M^-1 r; partial sums of (u, r), (u, u),
+//                (r, r).
 //
-// Unlike Algorithm 2, each of the two reductions gates the next launch, so
-// they cannot be hidden behind other work: they run as one-workgroup-per-
-// system kernels between the streaming kernels (no grid-wide fences or
-// atomics).  Which buffer of the pair holds the current direction follows
+// Every workgroup reads the same records in the same order, so all obtain the
+// same scalars bit for bit without a launch of their own for each reduction
+// (k_pcg_vma's partials gate k_pcg_spmv and the other way round).  A launch
+// reads the scalar state from one of two records and its tile 0 writes the
+// other: k_pcg_spmv reads rec[1] and writes rec[0], k_pcg_vma reads rec[0] and
+// writes rec[1].  A chunk of iterations starts from the canonical state (its
+// first k_pcg_spmv reduces nothing: beta is there) and ends with
+// k_pcg_update<PCG_ITER>, which reduces the last partials into it.
+//
+// The reductions used to be one-workgroup launches between the streaming
+// kernels.  Measured, us per iteration, four launches with 512-row tiles
+// against two: 27-point 128^3 in FP32 84 / 79 (59 + 14 us in the kernels; 225
+// MB of values and 100 MB of vectors), 7-point 97 x 131 x 75 in FP64 45 / 28
+// (16.7 + 11.2 us; there the chunk lists also replace 56 bytes of values per
+// row).  The SpMV cannot start before beta, which costs it the length of that
+// chain (about 4 us) where the one-workgroup launches cost 10 and two gaps.
+//
+// Which buffer of the pair holds the current direction follows
 // from the iteration counter: the SpMV of the iteration after k x-updates
 // reads buffer k mod 2 (p for even, z for odd) and writes the other.
 //
@@ -85,6 +100,37 @@ __device__ __forceinline__ void pcg_reduce(const SysDesc &d, int slot, double (&
             }
     }
     block_sum<kPcgRedThreads, NV>(out, lds);
+}
+
+// NV sums over the system's tiles from slot `slot` of the iteration's records
+// (4 doubles per tile of frows rows), as k_fused: thread t takes the tiles t,
+// t + NT, ... in index order, then the workgroup tree; valid in thread 0.
+// pcg_first_record issues the first loads, ahead of the stop check.
+template <int NV>
+__device__ __forceinline__ void pcg_first_record(const SysDesc &d, int slot, double (&v)[NV])
+{
+    const PPCG_AS1 double *P = as_global(d.part + (size_t)slot * d.ntiles * kPartStride);
+#pragma unroll
+    for (int k = 0; k < NV; ++k)
+        v[k] = 0.0;
+    if ((int)threadIdx.x < d.nftiles) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            v[k] = P[(size_t)threadIdx.x * 4 + k];
+    }
+    __asm__ volatile("" ::: "memory");
+}
+
+template <int NT, int NV>
+__device__ __forceinline__ void pcg_tile_sums(const SysDesc &d, int slot, double (&v)[NV], double *lds)
+{
+    const PPCG_AS1 double *P = as_global(d.part + (size_t)slot * d.ntiles * kPartStride);
+    for (int t = threadIdx.x + NT; t < d.nftiles; t += NT) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            v[k] = v[k] + P[(size_t)t * 4 + k];
+    }
+    block_sum<NT, NV>(v, lds);
 }
 
 // Direction buffers: the current direction after k x-updates is in pcg_dir(k).
@@ -228,8 +274,63 @@ __device__ __forceinline__ T pcg_sell_row(const SysDesc &d, const VT *__restrict
     return y;
 }
 
-// s = A p for one tile with p = u + beta p_old formed per gathered entry;
-// returns this thread's share of (s, p).
+// The same row on chunk lists (ppcg_lists.hpp): values VT as the per-entry
+// storage holds them.
+__device__ __forceinline__ double st_load_t(StBuf b, int byte, double)
+{
+    return st_load(b, byte);
+}
+__device__ __forceinline__ float st_load_t(StBuf b, int byte, float)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(b, byte, 0, 0));
+}
+
+template <int L, typename T, typename VT>
+__device__ __forceinline__ T pcg_list_span(const StLists p, int k0, StBuf u, StBuf po, int rowb, T beta, T y)
+{
+    T x[L], q[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+        const int o = rowb + p.off[k0 + j] / (int)(8 / sizeof(T));
+        x[j] = st_load_t(u, o, T());
+        q[j] = st_load_t(po, o, T());
+    }
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+        const bool has = __builtin_amdgcn_inverse_ballot_w64(p.mask[k0 + j]);
+        const T v = x[j] + beta * q[j];
+        y = y + (T)(VT)p.val[k0 + j] * (has ? v : (T)0);
+    }
+    return y;
+}
+
+template <int M, typename T, typename VT>
+__device__ __forceinline__ T pcg_list_tail(int rem, const StLists p, int k0, StBuf u, StBuf po, int rowb, T beta, T y)
+{
+    if constexpr (M > 0) {
+        if (rem == M)
+            return pcg_list_span<M, T, VT>(p, k0, u, po, rowb, beta, y);
+        return pcg_list_tail<M - 1, T, VT>(rem, p, k0, u, po, rowb, beta, y);
+    } else {
+        return y;
+    }
+}
+
+template <typename T, typename VT>
+__device__ __forceinline__ T pcg_list_row(const SysDesc &d, StChunk ch, StBuf u, StBuf po, int rowb, T beta)
+{
+    constexpr int B = 8;
+    const int len = ch[2];
+    const StLists p{as_constant(d.soff) + ch[0], as_constant(d.sval) + ch[0], as_constant(d.smask) + ch[1]};
+    T y = 0;
+    int k0 = 0;
+    for (; k0 + B <= len; k0 += B)
+        y = pcg_list_span<B, T, VT>(p, k0, u, po, rowb, beta, y);
+    return pcg_list_tail<B - 1, T, VT>(len - k0, p, k0, u, po, rowb, beta, y);
+}
+
+// s = A p for one tile of frows rows with p = u + beta p_old formed per
+// gathered entry; returns this thread's share of (s, p).
 template <typename T, typename VT>
 __device__ __forceinline__ double pcg_spmv_tile(const SysDesc &d, const WorkItem wi, const VT *__restrict__ val,
                                                 T beta, const PPCG_AS1 T *__restrict__ U,
@@ -237,18 +338,24 @@ __device__ __forceinline__ double pcg_spmv_tile(const SysDesc &d, const WorkItem
                                                 PPCG_AS1 T *__restrict__ S)
 {
     const int n = d.n;
+    const int row0 = wi.tile * d.frows, row1 = min(row0 + d.frows, n);
     double acc = 0.0;
     if (d.fmt == FMT_SELL) {
         const int lane = threadIdx.x & 63;
-        const int chunk = wi.tile * kSellChunksPerTile + (threadIdx.x >> 6);
-        const int i = chunk * kSellC + lane;
-        if (chunk * kSellC < n) {
-            // 16-bit columns measured slower for FP32 values with FP64
-            // vectors (27-point case, 263 vs 242 ms), so that mix reads 32-bit ones
-            const bool c16 = d.col16 && (PPCG_PCG_V32_COL16 || !(sizeof(T) == 8 && sizeof(VT) == 4));
-            const T y = d.cpat ? pcg_sell_row<2>(d, val, chunk, lane, beta, U, Pold)
-                        : c16  ? pcg_sell_row<1>(d, val, chunk, lane, beta, U, Pold)
-                               : pcg_sell_row<0>(d, val, chunk, lane, beta, U, Pold);
+        const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        // 16-bit columns measured slower for FP32 values with FP64
+        // vectors (27-point case, 263 vs 242 ms), so that mix reads 32-bit ones
+        const bool c16 = d.col16 && (PPCG_PCG_V32_COL16 || !(sizeof(T) == 8 && sizeof(VT) == 4));
+        const StBuf ub = __builtin_amdgcn_make_buffer_rsrc((void *)U, 0, n * (int)sizeof(T), 0x00020000);
+        const StBuf pb = __builtin_amdgcn_make_buffer_rsrc((void *)Pold, 0, n * (int)sizeof(T), 0x00020000);
+#pragma unroll 1
+        for (int c0 = row0 + wave * kSellC; c0 < row1; c0 += kSpmvThreads) {
+            const int chunk = c0 / kSellC, i = c0 + lane;
+            const T y = d.schunk ? pcg_list_row<T, VT>(d, as_constant((const StChunk *)d.schunk)[chunk], ub, pb,
+                                                       i * (int)sizeof(T), beta)
+                        : d.cpat ? pcg_sell_row<2>(d, val, chunk, lane, beta, U, Pold)
+                        : c16    ? pcg_sell_row<1>(d, val, chunk, lane, beta, U, Pold)
+                                 : pcg_sell_row<0>(d, val, chunk, lane, beta, U, Pold);
             if (i < n) {
                 const T pn = U[i] + beta * Pold[i];
                 Pnew[i] = pn;
@@ -260,9 +367,8 @@ __device__ __forceinline__ double pcg_spmv_tile(const SysDesc &d, const WorkItem
         const int L = d.lanes;
         const int g = threadIdx.x / L, l = threadIdx.x % L;
         const int rows_per_pass = kSpmvThreads / L;
-        const int passes = kTileRows / rows_per_pass;
-        for (int pass = 0; pass < passes; ++pass) {
-            const int i = wi.tile * kTileRows + pass * rows_per_pass + g;
+        for (int i0 = row0; i0 < row1; i0 += rows_per_pass) {  // frows is a whole number of passes
+            const int i = i0 + g;
             T y = 0;
             if (i < n) {
                 const int e = as_global(d.rp)[i + 1];
@@ -284,76 +390,6 @@ __device__ __forceinline__ double pcg_spmv_tile(const SysDesc &d, const WorkItem
     return acc;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kSpmvThreads, 8) void k_pcg_spmv(const WorkItem *__restrict__ table,
-                                                              const int *__restrict__ count,
-                                                              const SysDesc *__restrict__ descs, int remap)
-{
-    __shared__ double lds[kSpmvThreads / 64];
-    // Graphs bake a grid that may exceed the live table: blocks past it exit,
-    // and the XCD-aware order is taken over the live items only, so that
-    // every XCD gets an equal share of them.
-    const int live = *count;
-    if ((int)blockIdx.x >= live)
-        return;
-    const int pos = remap ? xcd_remap(blockIdx.x, live) : (int)blockIdx.x;
-    const WorkItem wi = table[pos];
-    const SysDesc &d = descs[wi.slot];
-    const SysState *st = d.st;
-    if (st->done)
-        return;
-    const T beta = (T)st->beta;
-    const int k = st->iter;
-    const PPCG_AS1 T *U = as_global((const T *)d.u);
-    // beta = 0 (a start, or a restart after a breakdown): read u in place of
-    // the old direction, so that whatever that buffer holds cannot leak in
-    // through 0 * Inf or 0 * NaN; u + 0 u = u exactly.
-    const PPCG_AS1 T *Pold = beta == (T)0 ? U : as_global((const T *)pcg_dir<T>(d, k));
-    PPCG_AS1 T *Pnew = as_global(pcg_dir<T>(d, k + 1));
-    PPCG_AS1 T *S = as_global((T *)d.s);
-    double v[1];
-    // FP32 vectors come with FP32 values (d.val); FP64 vectors use the FP32
-    // copy in FP32-values mode.
-    if (sizeof(T) == 4 || d.vals32)
-        v[0] = pcg_spmv_tile<T, float>(d, wi, sizeof(T) == 4 ? (const float *)d.val : d.val32, beta, U, Pold,
-                                       Pnew, S);
-    else
-        v[0] = pcg_spmv_tile<T, double>(d, wi, (const double *)d.val, beta, U, Pold, Pnew, S);
-    block_sum<kSpmvThreads, 1>(v, lds);
-    if (threadIdx.x == 0)
-        d.part[(size_t)wi.tile * kPartStride] = v[0];  // slot 0
-}
-
-// alpha = gamma / (s, p), with breakdown when gamma <= 0, (s, p) <= 0 or a
-// scalar is not finite.  One workgroup per system: the work items name
-// systems (tile 0); items of other tiles exit at once, so a tile table works
-// too.
-__global__ __launch_bounds__(kPcgRedThreads) void k_pcg_alpha(const WorkItem *__restrict__ systab,
-                                                              const int *__restrict__ count,
-                                                              const SysDesc *__restrict__ descs)
-{
-    __shared__ double lds[kPcgRedThreads / 64];
-    if ((int)blockIdx.x >= *count || systab[blockIdx.x].tile != 0)
-        return;
-    const SysDesc &d = descs[systab[blockIdx.x].slot];
-    SysState *st = d.st;
-    if (st->done)
-        return;
-    double dl[1];
-    pcg_reduce<1>(d, 0, dl, lds);
-    if (threadIdx.x == 0) {
-        const double g = st->gamma, beta = st->beta;
-        const double alpha = g / dl[0];
-        st->delta = dl[0];
-        if (!(g > 0.0) || !(dl[0] > 0.0) || !isfinite(alpha) || !isfinite(beta)) {
-            st->done = 1;
-            st->status = ST_BREAKDOWN;
-            return;
-        }
-        st->alpha = alpha;
-    }
-}
-
 enum PcgUpdate { PCG_START = 0, PCG_ITER = 1, PCG_REPL = 2 };
 
 // Stopping test at the top of Algorithm 1's loop and beta for the next
@@ -361,15 +397,13 @@ enum PcgUpdate { PCG_START = 0, PCG_ITER = 1, PCG_REPL = 2 };
 // follows an x-update; PCG_REPL follows a reliable update: the counters stay,
 // and beta = (u', r') / gamma_{i-1} with the replaced residual, the direction
 // being kept.
-__device__ inline void pcg_scalar_update(const SysDesc &d, SysState *st, const double (&v)[kNumPartials],
-                                         int kind)
+__device__ inline void pcg_scalar_update(const SysDesc &d, SysState *st, double g, double uu, double rr, int kind)
 {
     if (kind == PCG_ITER) {
         st->iter += 1;
         st->i_start += 1;
         st->gamma_prev = st->gamma;
     }
-    const double g = v[0], uu = v[1], rr = v[2];
     st->gamma = g;
     st->uu = uu;
     st->rr = rr;
@@ -404,13 +438,30 @@ __device__ inline void pcg_scalar_update(const SysDesc &d, SysState *st, const d
     st->beta = kind == PCG_START || st->i_start == 0 ? 0.0 : g / st->gamma_prev;
 }
 
-template <typename T>
-__global__ __launch_bounds__(kVmaThreads) void k_pcg_vma(const WorkItem *__restrict__ table,
-                                                         const int *__restrict__ count,
-                                                         const SysDesc *__restrict__ descs, int remap)
+// The scalar record of a launch in LDS: read by 32 threads, updated by thread
+// 0, written by 32 threads of tile 0.  (A record in thread 0's registers is
+// put into LDS by the compiler anyway, one copy per thread.)
+constexpr int kRecWords = sizeof(SysState) / sizeof(int);
+static_assert(kRecWords == 32, "one word per thread");
+__device__ __forceinline__ void pcg_rec_load(SysState *lds, const SysState *rec)
 {
-    using V2 = typename Vec2<T>::type;
-    __shared__ double lds[kVmaThreads / 64 * kNumPartials];
+    if (threadIdx.x < kRecWords)
+        ((int *)lds)[threadIdx.x] = as_global((const int *)rec)[threadIdx.x];
+}
+__device__ __forceinline__ void pcg_rec_store(SysState *rec, const SysState *lds)
+{
+    if (threadIdx.x < kRecWords)
+        as_global((int *)rec)[threadIdx.x] = ((const int *)lds)[threadIdx.x];
+}
+
+// first: the first iteration of a chunk, from the canonical state.
+template <typename T>
+__global__ __launch_bounds__(kSpmvThreads, 8) void k_pcg_spmv(const WorkItem *__restrict__ table,
+                                                              const int *__restrict__ count,
+                                                              const SysDesc *__restrict__ descs, int remap, int first)
+{
+    __shared__ double lds[kSpmvThreads / 64 * 3];
+    __shared__ SysState loc;
     // Graphs bake a grid that may exceed the live table: blocks past it exit,
     // and the XCD-aware order is taken over the live items only, so that
     // every XCD gets an equal share of them.
@@ -420,57 +471,163 @@ __global__ __launch_bounds__(kVmaThreads) void k_pcg_vma(const WorkItem *__restr
     const int pos = remap ? xcd_remap(blockIdx.x, live) : (int)blockIdx.x;
     const WorkItem wi = table[pos];
     const SysDesc &d = descs[wi.slot];
-    const SysState *st = d.st;
-    if (st->done)
+    const SysState *rin = first ? d.st : d.prs + 1;
+    pcg_rec_load(&loc, rin);
+    double v[3];
+    pcg_first_record<3>(d, 1, v);
+    if (as_constant(rin)->done) {  // k_pcg_vma reads the stop from the other record
+        if (wi.tile == 0)  // (each thread stores the word it loaded)
+            pcg_rec_store(d.prs, &loc);
         return;
-    const T alpha = (T)st->alpha;
+    }
+    if (!first) {
+        pcg_tile_sums<kSpmvThreads, 3>(d, 1, v, lds);
+        if (threadIdx.x == 0)
+            pcg_scalar_update(d, &loc, v[0], v[1], v[2], PCG_ITER);
+    }
+    __syncthreads();
+    if (wi.tile == 0)
+        pcg_rec_store(d.prs, &loc);
+    if (loc.done)
+        return;
+    const T beta = (T)loc.beta;
+    const int k = __builtin_amdgcn_readfirstlane(loc.iter);
+    const PPCG_AS1 T *U = as_global((const T *)d.u);
+    // beta = 0 (a start, or a restart after a breakdown): read u in place of
+    // the old direction, so that whatever that buffer holds cannot leak in
+    // through 0 * Inf or 0 * NaN; u + 0 u = u exactly.
+    const bool zero = __builtin_amdgcn_readfirstlane(beta == (T)0 ? 1 : 0) != 0;
+    const PPCG_AS1 T *Pold = zero ? U : as_global((const T *)pcg_dir<T>(d, k));
+    PPCG_AS1 T *Pnew = as_global(pcg_dir<T>(d, k + 1));
+    PPCG_AS1 T *S = as_global((T *)d.s);
+    double sp[1];
+    // FP32 vectors come with FP32 values (d.val); FP64 vectors use the FP32
+    // copy in FP32-values mode.
+    if (sizeof(T) == 4 || d.vals32)
+        sp[0] = pcg_spmv_tile<T, float>(d, wi, sizeof(T) == 4 ? (const float *)d.val : d.val32, beta, U, Pold,
+                                        Pnew, S);
+    else
+        sp[0] = pcg_spmv_tile<T, double>(d, wi, (const double *)d.val, beta, U, Pold, Pnew, S);
+    __syncthreads();  // lds reuse
+    block_sum<kSpmvThreads, 1>(sp, lds);
+    if (threadIdx.x == 0)
+        d.part[(size_t)wi.tile * 4] = sp[0];  // slot 0
+}
+
+constexpr int kPcgVmaThreads = 512;
+
+// alpha = gamma / (s, p), with breakdown when gamma <= 0, (s, p) <= 0 or a
+// scalar is not finite; then the updates.
+template <typename T>
+__global__ __launch_bounds__(kPcgVmaThreads) void k_pcg_vma(const WorkItem *__restrict__ table,
+                                                            const int *__restrict__ count,
+                                                            const SysDesc *__restrict__ descs, int remap)
+{
+    using V2 = typename Vec2<T>::type;
+    __shared__ double lds[kPcgVmaThreads / 64 * 3];
+    __shared__ SysState loc;
+    const int live = *count;
+    if ((int)blockIdx.x >= live)
+        return;
+    const int pos = remap ? xcd_remap(blockIdx.x, live) : (int)blockIdx.x;
+    const WorkItem wi = table[pos];
+    const SysDesc &d = descs[wi.slot];
+    const SysState *rin = d.prs;
+    const auto *rc = as_constant(rin);
+    pcg_rec_load(&loc, rin);
+    double v[1];
+    pcg_first_record<1>(d, 0, v);
+    if (rc->done) {
+        if (wi.tile == 0)
+            pcg_rec_store(d.prs + 1, &loc);
+        return;
+    }
+    const int n = d.n, row0 = wi.tile * d.frows, row1 = min(row0 + d.frows, n);
     PPCG_AS1 T *__restrict__ X = as_global((T *)d.x);
     PPCG_AS1 T *__restrict__ R = as_global((T *)d.r);
     PPCG_AS1 T *__restrict__ U = as_global((T *)d.u);
-    const PPCG_AS1 T *__restrict__ P = as_global((const T *)pcg_dir<T>(d, st->iter + 1));
+    const PPCG_AS1 T *__restrict__ P = as_global((const T *)pcg_dir<T>(d, rc->iter + 1));
     const PPCG_AS1 T *__restrict__ S = as_global((const T *)d.s);
     const PPCG_AS1 T *__restrict__ DI = as_global((const T *)d.dinv);
-    double acc[kNumPartials] = {0.0, 0.0, 0.0, 0.0};
-    auto elem = [&](T &x, T &r, T &u, T p, T sv, T di) {
-        x = x + alpha * p;
-        r = r - alpha * sv;
-        u = di * r;
-        const double rd = (double)r, ud = (double)u;
+    const bool dc = d.dinv_const != 0;
+    using CV2 = const PPCG_AS1 V2;
+    using GV2 = PPCG_AS1 V2;
+    // the first rows' operands, in flight beside the reduction
+    int i = row0 + threadIdx.x * 2;
+    V2 x = {0, 0}, r = {0, 0}, p = {0, 0}, sv = {0, 0};
+    if (i + 1 < row1) {
+        x = *(CV2 *)(X + i);
+        r = *(CV2 *)(R + i);
+        p = *(CV2 *)(P + i);
+        sv = *(CV2 *)(S + i);
+    }
+    {
+        pcg_tile_sums<kPcgVmaThreads, 1>(d, 0, v, lds);
+        if (threadIdx.x == 0) {
+            const double g = loc.gamma, beta = loc.beta, alpha = g / v[0];
+            loc.delta = v[0];
+            if (!(g > 0.0) || !(v[0] > 0.0) || !isfinite(alpha) || !isfinite(beta)) {
+                loc.done = 1;
+                loc.status = ST_BREAKDOWN;
+            } else {
+                loc.alpha = alpha;
+            }
+        }
+        __syncthreads();
+    }
+    if (wi.tile == 0)
+        pcg_rec_store(d.prs + 1, &loc);
+    if (loc.done)
+        return;
+    const T alpha = (T)loc.alpha;
+    double acc[3] = {0.0, 0.0, 0.0};
+    auto elem = [&](T &xj, T &rj, T &uj, T pj, T sj, T di) {
+        xj = xj + alpha * pj;
+        rj = rj - alpha * sj;
+        uj = di * rj;
+        const double rd = (double)rj, ud = (double)uj;
         acc[0] = acc[0] + ud * rd;
         acc[1] = acc[1] + ud * ud;
         acc[2] = acc[2] + rd * rd;
     };
-    const int i = wi.tile * kTileRows + threadIdx.x * 2;
-    if (i + 1 < d.n) {
-        using CV2 = const PPCG_AS1 V2;
-        using GV2 = PPCG_AS1 V2;
-        V2 x = vload((CV2 *)(X + i)), r = vload((CV2 *)(R + i));
-        const V2 p = vload((CV2 *)(P + i)), sv = vload((CV2 *)(S + i));
-        // a constant diagonal: every lane reads dinv[0..1] (one cached line)
-        const V2 di = vload((CV2 *)(DI + (d.dinv_const ? 0 : i)));
-        V2 u;
+    for (;;) {
+        if (i + 1 < row1) {
+            // a constant diagonal: every lane reads dinv[0..1] (one cached line)
+            const V2 di = *(CV2 *)(DI + (dc ? 0 : i));
+            V2 u;
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            T xj = x[j], rj = r[j], uj;
-            elem(xj, rj, uj, p[j], sv[j], di[j]);
-            x[j] = xj;
-            r[j] = rj;
-            u[j] = uj;
+            for (int j = 0; j < 2; ++j) {
+                T xj = x[j], rj = r[j], uj;
+                elem(xj, rj, uj, p[j], sv[j], di[j]);
+                x[j] = xj;
+                r[j] = rj;
+                u[j] = uj;
+            }
+            *(GV2 *)(X + i) = x;
+            *(GV2 *)(R + i) = r;
+            *(GV2 *)(U + i) = u;
+        } else if (i < row1) {
+            T xj = X[i], rj = R[i], uj;
+            elem(xj, rj, uj, P[i], S[i], DI[dc ? 0 : i]);
+            X[i] = xj;
+            R[i] = rj;
+            U[i] = uj;
         }
-        vstore((GV2 *)(X + i), x);
-        vstore((GV2 *)(R + i), r);
-        vstore((GV2 *)(U + i), u);
-    } else if (i < d.n) {
-        T x = X[i], r = R[i], u;
-        elem(x, r, u, P[i], S[i], DI[d.dinv_const ? 0 : i]);
-        X[i] = x;
-        R[i] = r;
-        U[i] = u;
+        i += 2 * kPcgVmaThreads;
+        if (i >= row1)
+            break;
+        if (i + 1 < row1) {
+            x = *(CV2 *)(X + i);
+            r = *(CV2 *)(R + i);
+            p = *(CV2 *)(P + i);
+            sv = *(CV2 *)(S + i);
+        }
     }
-    block_sum<kVmaThreads, kNumPartials>(acc, lds);
+    __syncthreads();  // lds reuse
+    block_sum<kPcgVmaThreads, 3>(acc, lds);
     if (threadIdx.x == 0) {
-        double *out = d.part + ((size_t)d.ntiles + wi.tile) * kPartStride;  // slot 1
-        for (int k = 0; k < kNumPartials; ++k)
+        double *out = d.part + (size_t)d.ntiles * kPartStride + (size_t)wi.tile * 4;  // slot 1
+        for (int k = 0; k < 3; ++k)
             out[k] = acc[k];
     }
 }
@@ -511,10 +668,12 @@ __global__ __launch_bounds__(kVmaThreads) void k_pcg_dots(const WorkItem *__rest
     }
 }
 
-// Reduce the update's partial sums and run the scalar update of the given
-// kind.  One workgroup per system.  After k_pcg_vma (PCG_ITER) only systems
-// still iterating take part; after k_pcg_dots (PCG_START, PCG_REPL) the
-// system's state is set up again, (b, b) included.
+// Reduce the partial sums and run the scalar update of the given kind.  One
+// workgroup per system: the work items name systems (tile 0); items of other
+// tiles exit at once, so a tile table works too.  PCG_ITER, the end of a chunk
+// of iterations: the last k_pcg_vma's sums and record into the canonical
+// state.  PCG_START, PCG_REPL, after k_pcg_dots: the system's state is set up
+// again, (b, b) included.
 template <int KIND>
 __global__ __launch_bounds__(kPcgRedThreads) void k_pcg_update(const WorkItem *__restrict__ systab,
                                                                const int *__restrict__ count,
@@ -525,20 +684,30 @@ __global__ __launch_bounds__(kPcgRedThreads) void k_pcg_update(const WorkItem *_
         return;
     const SysDesc &d = descs[systab[blockIdx.x].slot];
     SysState *st = d.st;
-    if (KIND == PCG_ITER && st->done)
-        return;
-    double v[kNumPartials];
-    pcg_reduce<kNumPartials>(d, 1, v, lds);
-    if (threadIdx.x == 0) {
-        if (KIND != PCG_ITER) {
+    if constexpr (KIND == PCG_ITER) {
+        __shared__ SysState loc;
+        pcg_rec_load(&loc, d.prs + 1);
+        double v[3];
+        pcg_first_record<3>(d, 1, v);
+        if (!as_constant((const SysState *)d.prs)[1].done) {
+            pcg_tile_sums<kPcgRedThreads, 3>(d, 1, v, lds);
+            if (threadIdx.x == 0)
+                pcg_scalar_update(d, &loc, v[0], v[1], v[2], KIND);
+        }
+        __syncthreads();
+        pcg_rec_store(st, &loc);
+    } else {
+        double v[kNumPartials];
+        pcg_reduce<kNumPartials>(d, 1, v, lds);
+        if (threadIdx.x == 0) {
             st->bnorm2 = v[3];
             st->phase = 0;
+            // A reliable update after a breakdown restarts the direction (beta = 0)
+            // from the replaced residual: the kept direction is not usable.
+            if (KIND == PCG_REPL && st->status == ST_BREAKDOWN)
+                st->i_start = 0;
+            pcg_scalar_update(d, st, v[0], v[1], v[2], KIND);
         }
-        // A reliable update after a breakdown restarts the direction (beta = 0)
-        // from the replaced residual: the kept direction is not usable.
-        if (KIND == PCG_REPL && st->status == ST_BREAKDOWN)
-            st->i_start = 0;
-        pcg_scalar_update(d, st, v, KIND);
     }
 }
 

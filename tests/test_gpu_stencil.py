@@ -122,6 +122,23 @@ def test_spmv_and_initial_guess_on_lists(name):
         s.close()
 
 
+@pytest.mark.parametrize("gen", [lambda: poisson2d(67), lambda: box(63, 9, 11), lambda: poisson3d(40)])
+@pytest.mark.parametrize("prec", ["fp64", "mixed", "mixed_values"])
+def test_classic_pcg_on_lists(gen, prec):
+    """Algorithm 1 reads the lists in every precision (FP32 values are the rounded list values): bit for bit the
+    per-entry columns' solve, with the tiles of its two launches ragged at these sizes."""
+    A = gen()
+    b = rhs_from_solution(A, xstar_uniform(A.n, 6))
+    res = []
+    for flags in (ppcg.FLAG_SELL_SHARED_OFFSETS, ppcg.FLAG_SELL_NO_SHARED_OFFSETS):
+        S = Solver(A, tol=1e-10, method="pcg", precision=prec, spmv_format="sell", flags=flags)
+        x, info = S.solve(dev(b))
+        assert info["status"] == ppcg.OK and oracle.true_relres(A, b, host(x)) <= 1e-10
+        res.append((host(x), info["iters"], info["outer_iters"]))
+        S.close()
+    assert np.array_equal(res[0][0], res[1][0]) and res[0][1:] == res[1][1:]
+
+
 def test_batch_of_list_and_column_systems_equals_solo_bitwise():
     """Both kernels in one batch, twice (captured graphs replayed), with systems that end at different times."""
     mats = [poisson2d(80), shifted(poisson2d(121), 0.3), poisson3d(33), box(31, 17, 20), poisson2d(40)]
