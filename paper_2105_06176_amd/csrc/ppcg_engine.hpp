@@ -123,6 +123,7 @@ struct ppcg_handle {
     int *soff = nullptr;
     double *sval = nullptr;
     unsigned long long *smask = nullptr;
+    int smaxlen = 0;
     ppcg::DevArena st_arena;
     int *perm = nullptr, *invperm = nullptr;
     double *val64 = nullptr;  // FP64 values in the stored format

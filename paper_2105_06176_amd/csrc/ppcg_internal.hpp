@@ -258,6 +258,7 @@ struct SysDesc {
     const unsigned long long *smask;  // the lanes whose row has it
     double *shist;        // 2 slots (launch parity) of alpha[kStDefer], beta[kStDefer]
     int vstride;          // bytes between two of the FP64 vectors x r u w m nv z q s p
+    int smaxlen;          // entries of the longest list
     int sring;            // 1: k_stencil keeps kStDefer residuals and updates p and x together
     const void *val;      // matrix values (double or float)
     const float *val32;   // FP32 copy of the values (vals32 mode)

@@ -168,9 +168,9 @@ static ByteModel byte_model(const ppcg_handle *h, int prec)
     const bool sh = h->shared_on;
     const double ie = sh ? 0.0 : (h->col16 && (PPCG_PCG_V32_COL16 || !(pcg && prec == PREC_V32))) ? 2.0 : 4.0;
     bm.spmv = (me + ie) * (double)h->nnz + ptr + (sh ? 4.0 * h->nchunks : 0.0) + (pcg ? 4.0 : 2.0) * ve * n;
-    // classic PCG on chunk lists: 16 bytes per chunk stand for the matrix
-    if (h->schunk && pcg)
-        bm.spmv = 16.0 * h->nchunks + 4.0 * ve * n;
+    // on chunk lists 16 bytes per chunk stand for the matrix
+    if (h->schunk)
+        bm.spmv = 16.0 * h->nchunks + (pcg ? 4.0 : 2.0) * ve * n;
     // the single-launch form keeps n in registers (neither written by the
     // SpMV nor read by the update) and, with a constant diagonal, forms
     // m = M^-1 w in the next launch's gathers instead of writing it (the
@@ -178,15 +178,11 @@ static ByteModel byte_model(const ppcg_handle *h, int prec)
     if (h->form == FORM_FUSED && prec == PREC_F64 && !pcg) {
         bm.vma -= (h->dinv_const ? 2.0 : 1.0) * ve * n;
         bm.spmv -= ve * n;
-        // chunks described by lists: 16 bytes per chunk stand for the matrix;
-        // with the ring, p (else read and written) and x (else every other
+        // k_stencil with the ring: p (else read and written) and x (else every other
         // launch) are read and written once in kStDefer launches, and the
         // older residuals read again
-        if (h->schunk) {
-            bm.spmv = 16.0 * h->nchunks + ve * n;
-            if (stencil_ring(h->n))
-                bm.vma += (4.0 / kStDefer + (kStDefer - 1.0) / kStDefer - 3.0) * ve * n;
-        }
+        if (h->schunk && stencil_ring(h->n))
+            bm.vma += (4.0 / kStDefer + (kStDefer - 1.0) / kStDefer - 3.0) * ve * n;
     }
     return bm;
 }
@@ -489,11 +485,12 @@ ppcg_status fill_desc(ppcg_handle *h, int prec, SysState *st, SysDesc *d, double
     d->nvtab = h->nvtab;
     d->cpat = h->shared_on ? h->cpat : nullptr;
     d->pats = h->pats;
-    if (h->form == FORM_FUSED) {
+    if (h->schunk) {
         d->schunk = h->schunk;
         d->soff = h->soff;
         d->sval = h->sval;
         d->smask = h->smask;
+        d->smaxlen = h->smaxlen;
         d->shist = h->shist;
         d->vstride = (int)((char *)pd.vec[VR] - (char *)pd.vec[VX]);
         d->sring = stencil_ring(h->n) ? 1 : 0;
@@ -1078,7 +1075,6 @@ static ppcg_status build_stencil(ppcg_handle *h)
 {
     const unsigned fl = h->opt.flags;
     if (h->fmt != FMT_SELL || !h->cpat || h->perm || !h->dinv_const || h->n > kStMaxRows ||
-        (h->n <= PPCG_SMALL_MAX_ROWS && !(fl & PPCG_FLAG_ITER_FUSED)) ||
         (fl & (PPCG_FLAG_SELL_COL16 | PPCG_FLAG_SELL_COL32 | PPCG_FLAG_SELL_NO_SHARED_OFFSETS |
                PPCG_FLAG_SELL_FULL_VALUES | PPCG_FLAG_ITER_TWO_LAUNCH)) != 0)
         return PPCG_OK;
@@ -1121,6 +1117,7 @@ static ppcg_status build_stencil(ppcg_handle *h)
     std::unordered_map<unsigned long long, int> lists, masks;
     std::vector<int4> chunk((size_t)nc), items;
     int64_t nlist = 0, nmask = 0;
+    int longest = 0;
     const int64_t cap = std::max<int64_t>(h->nnz_stored / 2, 65536);
     for (int c = 0; c < nc; ++c) {
         const int len = (int)((cp[c + 1] - cp[c]) / kSellC);
@@ -1137,6 +1134,7 @@ static ppcg_status build_stencil(ppcg_handle *h)
         if (12 * nlist + 8 * nmask > cap)
             return PPCG_OK;
         chunk[c] = make_int4(l.first->second, m.first->second, len, 0);
+        longest = std::max(longest, len);
     }
     if (!keep)
         PPCG_TRY(h->st_arena.alloc(16 * (size_t)nc + 12 * (size_t)nlist + 8 * (size_t)nmask + 8 * 256));
@@ -1163,6 +1161,7 @@ static ppcg_status build_stencil(ppcg_handle *h)
         drop_stencil(h);
     else
         h->schunk = schunk;
+    h->smaxlen = longest;
     PPCG_HIP(e);
     return PPCG_OK;
 }
@@ -1255,7 +1254,7 @@ static ppcg_status tune_form(ppcg_handle *h)
     const uint32_t f = h->opt.flags;
     if ((f & PPCG_FLAG_ITER_TWO_LAUNCH) || h->fmt != FMT_SELL)
         return PPCG_OK;
-    if ((f & PPCG_FLAG_ITER_FUSED) || h->schunk) {
+    if ((f & PPCG_FLAG_ITER_FUSED) || (h->schunk && h->n > PPCG_SMALL_MAX_ROWS)) {
         PPCG_TRY(ensure_fused(h));
         h->form = FORM_FUSED;
         return PPCG_OK;

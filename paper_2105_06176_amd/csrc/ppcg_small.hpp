@@ -11,206 +11,442 @@ namespace ppcg {
 // Small systems: one workgroup of kSmallThreads runs up to `iters` whole
 // PIPECG iterations of one system per launch (work item = system).  Thread t
 // owns the rows t, t + kSmallThreads, ... (at most kSmallRowsPerThread) and
-// keeps their z, q, s, p, r, u, w and n in registers for the whole launch;
-// m, the only vector other rows read (the SpMV gathers), and x live in LDS,
-// the scalar state record in LDS, the chunk extents in scalar registers.  An iteration touches global memory only for the matrix
-// and an inverse diagonal that is not constant (L2-resident at these sizes):
-// fused update, fixed-order workgroup reduction and scalar update (thread 0),
-// workgroup barrier, SpMV from LDS, barrier.  Vectors and the state are
-// loaded at the start and stored at the end of the launch, so the state in
-// HBM is complete between launches.  SELL
-// format only; rows of a wavefront form one SELL chunk, so chunk lengths are
-// uniform across each wavefront.
+// keeps their z, s, p, r, w, x and n in registers for the whole launch; m,
+// the only vector other rows read (the SpMV gathers), and the state record
+// live in LDS.  Vectors and the state are loaded at the start and stored at the end of the launch.
+// SELL format only; rows of a wavefront form one SELL chunk, so chunk lengths
+// are uniform across each wavefront.
 //
-// With the one-byte value table (the matrix has at most 256 distinct values)
-// and at most kSmallLdsEntries stored entries, the matrix itself is staged
-// in LDS at the start of the launch, each entry as a 16-bit column offset
-// from its row and its value index: the SpMV of an iteration then reads
-// nothing from global memory, and its steps over a row's entries wait on
-// LDS instead of L2 round trips.  Same values and order, so the same sums.
-constexpr int kSmallThreads = 512;
-constexpr int kSmallRowsPerThread = 8;
+// An iteration:
+//   update of the thread's rows, m into LDS, the four dot products summed per
+//   wavefront                                                    -- barrier --
+//   the last wavefront sums the wavefronts' sums and runs the scalar
+//   recurrences while all (it too, afterwards) compute n = A m from LDS: the
+//   overlap that Algorithm 2 is made for                         -- barrier --
+//
+// Where the matrix comes from, in order of preference:
+//   lists   offsets, values and masks of the chunk through scalar loads
+//           (ppcg_lists.hpp); an absent entry reads a slot that holds 0;
+//   staged  with the one-byte value table and at most kSmallLdsEntries stored
+//           entries, copied into LDS at the start of the launch, each entry
+//           as a 16-bit column offset from its row and its value index;
+//   memory  columns and values from L2.
+// Same values and order in all three, so the same sums.
+//
+// Bound by issue and by the reductions' chain on one compute unit.  64^2
+// 5-point, us per iteration: 512 threads with 8 rows each, the matrix staged,
+// the dot products summed one by one and the scalars before the SpMV 6.5; this
+// form 2.9 (4.7 with the lists read in every iteration and the scalars kept in
+// the LDS record).
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallRowsPerThread = 4;
 constexpr int kSmallMaxRows = kSmallThreads * kSmallRowsPerThread;
 constexpr int kSmallLdsEntries = 24576;
+constexpr int kSmallWaves = kSmallThreads / 64;
 static_assert(kSmallMaxRows <= 32768, "column offsets from the row fit 16 bits");
 static_assert(PPCG_SMALL_MAX_ROWS <= kSmallMaxRows, "small systems must fit the register-resident kernel");
 
-__global__ __launch_bounds__(kSmallThreads) void k_small_iter(const WorkItem *__restrict__ table,
-                                                              const int *__restrict__ count,
-                                                              const SysDesc *__restrict__ descs, int iters)
+// a + b after the upper half (SWAP 32) or the odd rows of 16 (SWAP 16) of a
+// changed places with the lower half or the even rows of b: lanes of the
+// first kind hold a's sum with its partner lane, the others b's.
+template <int SWAP>
+__device__ __forceinline__ double swap_add(double a, double b)
+{
+    const unsigned long long x = (unsigned long long)__double_as_longlong(a);
+    const unsigned long long y = (unsigned long long)__double_as_longlong(b);
+    uvec2 lo, hi;
+    if constexpr (SWAP == 32) {
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+        lo = uvec2{l[0], l[1]};
+        hi = uvec2{h[0], h[1]};
+    } else {
+        const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+        lo = uvec2{l[0], l[1]};
+        hi = uvec2{h[0], h[1]};
+    }
+    return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+           __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+// Sum over each row of 16 lanes, in every lane of the row.
+__device__ __forceinline__ double row_sum(double v)
+{
+    v = v + dpp_f64<0x128>(v);  // row_ror:8
+    v = v + dpp_f64<0x124>(v);  // row_ror:4
+    v = v + dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
+    v = v + dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
+    return v;
+}
+
+// The value of lane j (uniform) in every lane.
+__device__ __forceinline__ double readlane_f64(double v, int j)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, j);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), j);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// The wavefront's sums of four values at once: lane l ends with the sum of
+// v[l / 16].  Two exchanges halve the values each lane carries, where four
+// separate butterflies would add every value in every lane at every step
+// (7 additions and 14 moves instead of 24 and 48).  The pairs are those of
+// wave_sum, so each sum is bit for bit wave_sum's.
+__device__ __forceinline__ double wave_sum4(const double (&v)[kNumPartials])
+{
+    const double a = swap_add<32>(v[0], v[2]), b = swap_add<32>(v[1], v[3]);
+    return row_sum(swap_add<16>(a, b));
+}
+
+// Entries k0 .. k0 + L - 1 of a row from the lists: lane's row at byte rowb
+// of the LDS vector m, absent entries at byte zero.
+template <int L>
+__device__ __forceinline__ double small_span(const StLists p, int k0, const char *m, int rowb, int zero, double a)
+{
+    double x[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+        const bool has = __builtin_amdgcn_inverse_ballot_w64(p.mask[k0 + j]);
+        x[j] = *(const double *)(m + (has ? rowb + p.off[k0 + j] : zero));
+    }
+#pragma unroll
+    for (int j = 0; j < L; ++j)
+        a = a + p.val[k0 + j] * x[j];
+    return a;
+}
+
+template <int M>
+__device__ __forceinline__ double small_tail(int rem, const StLists p, int k0, const char *m, int rowb, int zero,
+                                             double a)
+{
+    if constexpr (M > 0) {
+        if (rem == M)
+            return small_span<M>(p, k0, m, rowb, zero, a);
+        return small_tail<M - 1>(rem, p, k0, m, rowb, zero, a);
+    } else {
+        return a;
+    }
+}
+
+// The shared memory of the workgroup.
+struct SmallLds {
+    double m[kSmallMaxRows + 1];  // the last element is 0
+    double part[kNumPartials * kSmallWaves];
+    double scal[2];  // alpha, beta of the next update
+    int stop;
+    SysState loc;    // the state record, written back at the end of the launch
+    short lco[kSmallLdsEntries];          // staged matrix: column - row
+    unsigned char lvi[kSmallLdsEntries];  // and value index
+    double ltab[kMaxValueTable];          // the value table
+};
+
+// scalar_update (ppcg_kernels.hpp) for FP64 PIPECG with what it reads kept in
+// registers: through the record in LDS every field costs a round trip of the
+// chain that all wavefronts wait for.
+struct SmallScalars {
+    double gamma_prev, alpha_prev, limit;  // limit: of the stopping quantity
+    int iter, i_start, phase;
+};
+
+__device__ __forceinline__ void small_scalars(const SysDesc &d, SmallScalars &c, const double (&v)[kNumPartials],
+                                              SmallLds &L)
+{
+    if (c.phase) {
+        c.phase = 0;
+    } else {
+        c.iter += 1;
+        c.i_start += 1;
+    }
+    const double g = v[0], dl = v[1];
+    L.loc.gamma_prev2 = c.gamma_prev;
+    L.loc.gamma = g;
+    L.loc.delta = dl;
+    L.loc.uu = v[2];
+    L.loc.rr = v[3];
+    bool conv;
+    if (d.fixed > 0)
+        conv = c.iter >= d.fixed || g == 0.0;
+    else if (d.stop == STOP_ABS)
+        conv = sqrt(v[2]) < c.limit;
+    else
+        conv = sqrt(v[3]) <= c.limit;
+    int status = -1;
+    double beta = 0.0, denom = dl;
+    if (c.i_start > 0) {
+        beta = g / c.gamma_prev;
+        denom = dl - beta * g / c.alpha_prev;
+    }
+    const double alpha = g / denom;
+    if (conv)
+        status = ST_OK;
+    else if (d.fixed <= 0 && c.iter >= d.maxit)
+        status = ST_NOT_CONVERGED;
+    else if (!(g > 0.0) || !(denom > 0.0) || !isfinite(alpha) || !isfinite(beta))
+        status = ST_BREAKDOWN;
+    if (status >= 0) {
+        L.loc.done = 1;
+        L.loc.status = status;
+        L.stop = 1;
+        return;
+    }
+    L.scal[0] = alpha;
+    L.scal[1] = beta;
+    c.gamma_prev = g;
+    c.alpha_prev = alpha;
+}
+
+// E > 0: chunk lists of at most E entries.  The LDS address of every entry of
+// the thread's rows is formed once (two 16-bit addresses per register), so an
+// iteration's gathers issue back to back and wait for nothing.  E = 0: any
+// other matrix, see above.
+template <int E>
+__device__ __forceinline__ void small_run(const SysDesc &d, int iters, SmallLds &L)
 {
     constexpr int R = kSmallRowsPerThread;
-    __shared__ double lds[kSmallThreads / 64 * kNumPartials];
-    __shared__ double lm[kSmallMaxRows];  // m
-    __shared__ double lx[kSmallMaxRows];  // x, written back at the end of the launch
-    __shared__ double scal[2];            // alpha, beta of the next update
-    __shared__ SysState loc;              // the state record, written back at the end of the launch
-    __shared__ int stop;
-    __shared__ short lco[kSmallLdsEntries];           // staged matrix: column - row
-    __shared__ unsigned char lvi[kSmallLdsEntries];   // and value index
-    __shared__ double ltab[kMaxValueTable];           // the value table
-    if ((int)blockIdx.x >= *count)
-        return;
-    const WorkItem wi = table[blockIdx.x];
-    const SysDesc &d = descs[wi.slot];
     SysState *st = d.st;
     const int n = d.n;
-    double *__restrict__ X = (double *)d.x;
-    double *__restrict__ Rv = (double *)d.r;
-    double *__restrict__ U = (double *)d.u;
-    double *__restrict__ W = (double *)d.w;
-    double *__restrict__ M = (double *)d.m;
-    double *__restrict__ NVv = (double *)d.nv;
-    double *__restrict__ Z = (double *)d.z;
-    double *__restrict__ S = (double *)d.s;
-    double *__restrict__ P = (double *)d.p;
-    const double *__restrict__ DI = (const double *)d.dinv;
-    const double *__restrict__ val = (const double *)d.val;
-    const int *__restrict__ col = d.col;
-    const int64_t *__restrict__ cptr = d.cptr;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    PPCG_AS1 double *__restrict__ X = as_global((double *)d.x);
+    PPCG_AS1 double *__restrict__ Rv = as_global((double *)d.r);
+    PPCG_AS1 double *__restrict__ Wv = as_global((double *)d.w);
+    PPCG_AS1 double *__restrict__ NVv = as_global((double *)d.nv);
+    PPCG_AS1 double *__restrict__ Z = as_global((double *)d.z);
+    PPCG_AS1 double *__restrict__ S = as_global((double *)d.s);
+    PPCG_AS1 double *__restrict__ P = as_global((double *)d.p);
+    const PPCG_AS1 double *__restrict__ DI = as_global((const double *)d.dinv);
+    const PPCG_AS1 double *__restrict__ val = as_global((const double *)d.val);
+    const PPCG_AS1 int *__restrict__ col = as_global(d.col);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double *const m = L.m;
     // u and q are scalings of r and s by the inverse diagonal (see vma_elem):
     // u is formed from r, q never
-    double z[R], s[R], p[R], r[R], u[R], w[R], nv[R];
+    double z[R], s[R], p[R], r[R], w[R], nv[R], x[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const int i = threadIdx.x + j * kSmallThreads;
+        const int i = tid + j * kSmallThreads;
         const bool ok = i < n;
         z[j] = ok ? Z[i] : 0.0;
         s[j] = ok ? S[i] : 0.0;
         p[j] = ok ? P[i] : 0.0;
         r[j] = ok ? Rv[i] : 0.0;
-        u[j] = ok ? U[i] : 0.0;  // written back unchanged if no iteration runs
-        w[j] = ok ? W[i] : 0.0;
+        w[j] = ok ? Wv[i] : 0.0;
         nv[j] = ok ? NVv[i] : 0.0;
-        if (ok) {
-            lm[i] = M[i];
-            lx[i] = X[i];
-        }
+        x[j] = ok ? X[i] : 0.0;
     }
-    // The state record lives in LDS for the launch (written back at its end),
-    // the chunk extents in scalar registers.
-    if (threadIdx.x == 0) {
-        loc = *st;
-        stop = loc.done;
-        scal[0] = loc.alpha;
-        scal[1] = loc.beta;
+    if (tid < (int)(sizeof(SysState) / sizeof(int)))
+        ((int *)&L.loc)[tid] = as_global((const int *)st)[tid];
+    if (tid == 0) {
+        L.stop = st->done;
+        L.scal[0] = st->alpha;
+        L.scal[1] = st->beta;
+        m[kSmallMaxRows] = 0.0;
     }
-    int base[R], len[R], maxlen = 0;
+    SmallScalars c{};
+    if (wave == kSmallWaves - 1) {
+        c.gamma_prev = st->gamma_prev;
+        c.alpha_prev = st->alpha_prev;
+        c.limit = d.stop == STOP_ABS ? d.tol : d.tol * sqrt(st->bnorm2);
+        c.iter = st->iter;
+        c.i_start = st->i_start;
+        c.phase = st->phase;
+    }
+    // chunk j of this wavefront: rows wave * 64 + j * kSmallThreads + lane
+    const bool lists = E > 0 || d.schunk != nullptr;
+    int base[R], len[R], msk[R], maxlen = 0;
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const int c = wave + j * (kSmallThreads / 64);
-        base[j] = 0;
-        len[j] = 0;
-        if (c * kSellC < n) {  // c is the same in every lane: scalar registers
-            base[j] = __builtin_amdgcn_readfirstlane((int)cptr[c]);
-            len[j] = __builtin_amdgcn_readfirstlane((int)((cptr[c + 1] - cptr[c]) / kSellC));
+        const int ci = wave + j * kSmallWaves;
+        base[j] = len[j] = msk[j] = 0;
+        if (ci * kSellC < n) {
+            if (lists) {
+                const StChunk ch = as_constant((const StChunk *)d.schunk)[ci];
+                base[j] = ch[0];
+                msk[j] = ch[1];
+                len[j] = ch[2];
+            } else {
+                base[j] = (int)as_constant(d.cptr)[ci];
+                len[j] = (int)((as_constant(d.cptr)[ci + 1] - as_constant(d.cptr)[ci]) / kSellC);
+            }
         }
         maxlen = len[j] > maxlen ? len[j] : maxlen;
     }
-    const bool dconst = d.dinv_const != 0;
-    const double d0 = DI[0];
+    unsigned adr[R][(E + 2) / 2] = {};
+    if constexpr (E > 0) {
+        static_assert(8 * (kSmallMaxRows + 1) <= 65536, "LDS addresses of m fit 16 bits");
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+#pragma unroll
+            for (int k = 0; k < E; ++k) {
+                const bool in = k < len[j];
+                const unsigned long long has = in ? as_constant(d.smask)[msk[j] + k] : 0ull;
+                const int o = in ? as_constant(d.soff)[base[j] + k] : 0;
+                const unsigned a = __builtin_amdgcn_inverse_ballot_w64(has)
+                                       ? (unsigned)((tid + j * kSmallThreads) * 8 + o)
+                                       : (unsigned)(kSmallMaxRows * 8);
+                adr[j][k / 2] |= (k & 1) ? a << 16 : a;
+            }
+    }
+    const bool dconst = E > 0 || d.dinv_const != 0;
+    const double d0 = as_constant((const double *)d.dinv)[0];
     // staged matrix (uniform over the workgroup)
-    const bool staged = d.vidx != nullptr && cptr[(n + kSellC - 1) / kSellC] <= kSmallLdsEntries;
+    const bool staged =
+        !lists && d.vidx != nullptr && as_constant(d.cptr)[(n + kSellC - 1) / kSellC] <= kSmallLdsEntries;
     if (staged) {
-        for (int t = threadIdx.x; t < d.nvtab; t += kSmallThreads)
-            ltab[t] = d.vtab[t];
+        for (int t = tid; t < d.nvtab; t += kSmallThreads)
+            L.ltab[t] = d.vtab[t];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const int row = threadIdx.x + j * kSmallThreads;
+            const int row = tid + j * kSmallThreads;
             for (int k = 0; k < len[j]; ++k) {
                 const int o = base[j] + lane + k * kSellC;
-                lco[o] = (short)(col[o] - row);
-                lvi[o] = d.vidx[o];
+                L.lco[o] = (short)(col[o] - row);
+                L.lvi[o] = d.vidx[o];
             }
         }
     }
     __syncthreads();
-    for (int it = 0; it < iters && !stop; ++it) {
-        const double sa = scal[0], sb = scal[1];
+    for (int it = 0; it < iters && !L.stop; ++it) {
+        const double sa = L.scal[0], sb = L.scal[1];
         double acc[kNumPartials] = {0.0, 0.0, 0.0, 0.0};
-        // the inverse diagonal: one value, or loaded first (one memory latency)
-        double dg[R];
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-            const int i = threadIdx.x + j * kSmallThreads;
-            dg[j] = d0;
-            if (!dconst && i < n)
-                dg[j] = DI[i];
-        }
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-            const int i = threadIdx.x + j * kSmallThreads;
+            const int i = tid + j * kSmallThreads;
             if (i < n) {
-                double mo;
-                vma_elem<double, kNumPartials>(sa, sb, nv[j], z[j], w[j], s[j], p[j], r[j], dg[j], u[j], mo, acc);
-                lx[i] = lx[i] + sa * p[j];  // this kernel updates x every iteration
-                lm[i] = mo;  // only this thread touches lm[i] and lx[i] until the barrier below
+                double di = d0;
+                if (!dconst)
+                    di = DI[i];
+                double u, mo;
+                vma_elem<double, kNumPartials>(sa, sb, nv[j], z[j], w[j], s[j], p[j], r[j], di, u, mo, acc);
+                x[j] = x[j] + sa * p[j];  // this kernel updates x every iteration
+                m[i] = mo;
             }
         }
-        block_sum<kSmallThreads, kNumPartials>(acc, lds);
-        if (threadIdx.x == 0) {
-            scalar_update<kNumPartials>(d, &loc, acc);
-            stop = loc.done;
-            scal[0] = loc.alpha;
-            scal[1] = loc.beta;
-        }
-        __syncthreads();  // m complete in LDS; the new scalars visible
-        // SpMV from LDS: the wavefront's chunk for row slot j is wave + j *
-        // (waves per workgroup); entry k of all its chunks is fetched together.
-        // (stored entries of a system with at most kSmallMaxRows rows fit 32 bits)
+        const double ws = wave_sum4(acc);
+        if ((lane & 15) == 0)
+            L.part[(lane >> 4) * kSmallWaves + wave] = ws;
+        __syncthreads();  // m and the wavefronts' sums complete
+        if (wave == kSmallWaves - 1) {
+            // lane k < 4: value k, the wavefronts in order
+            const double *q = L.part + (lane & 3) * kSmallWaves;
+            double t = q[0];
 #pragma unroll
-        for (int j = 0; j < R; ++j)
-            nv[j] = 0.0;
-        if (staged) {
+            for (int k = 1; k < kSmallWaves; ++k)
+                t = t + q[k];
+            const double v[kNumPartials] = {readlane_f64(t, 0), readlane_f64(t, 1), readlane_f64(t, 2),
+                                            readlane_f64(t, 3)};
+            small_scalars(d, c, v, L);
+        }
+        // n = A m (stored entries of a system with at most kSmallMaxRows rows
+        // fit 32 bits)
+        if constexpr (E > 0) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                // (read again in every iteration: 4 E values do not fit the scalar registers)
+                int b = base[j];
+                __asm__ volatile("" : "+s"(b));
+                double g[E], a = 0.0;
+#pragma unroll
+                for (int k = 0; k < E; ++k)
+                    g[k] = *(const double *)((const char *)m + ((k & 1) ? adr[j][k / 2] >> 16
+                                                                          : adr[j][k / 2] & 0xffffu));
+#pragma unroll
+                for (int k = 0; k < E; ++k)
+                    a = a + (k < len[j] ? as_constant(d.sval)[b + k] : 0.0) * g[k];
+                nv[j] = a;
+            }
+        } else if (lists) {
+#pragma unroll
+            for (int j = 0; j < R; ++j) {
+                if (len[j] > 0) {
+                    const StLists q{as_constant(d.soff) + base[j], as_constant(d.sval) + base[j],
+                                    as_constant(d.smask) + msk[j]};
+                    const int rowb = (tid + j * kSmallThreads) * 8;
+                    double a = 0.0;
+                    int k0 = 0;
+                    for (; k0 + 8 <= len[j]; k0 += 8)
+                        a = small_span<8>(q, k0, (const char *)m, rowb, kSmallMaxRows * 8, a);
+                    nv[j] = small_tail<7>(len[j] - k0, q, k0, (const char *)m, rowb, kSmallMaxRows * 8, a);
+                }
+            }
+        } else if (staged) {
+            // entry k of all the wavefront's chunks together
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                nv[j] = 0.0;
             for (int k = 0; k < maxlen; ++k) {
 #pragma unroll
                 for (int j = 0; j < R; ++j) {
                     if (k < len[j]) {
                         const int o = base[j] + lane + k * kSellC;
-                        nv[j] = nv[j] + ltab[lvi[o]] * lm[threadIdx.x + j * kSmallThreads + lco[o]];
+                        nv[j] = nv[j] + L.ltab[L.lvi[o]] * m[tid + j * kSmallThreads + L.lco[o]];
                     }
                 }
             }
-        }
-        for (int k = 0; k < (staged ? 0 : maxlen); ++k) {
-            // entry k of every row slot: loads first, then the LDS gathers
-            int cv[R];
-            double vv[R];
-#pragma unroll
-            for (int j = 0; j < R; ++j) {
-                cv[j] = 0;
-                vv[j] = 0.0;
-                if (k < len[j]) {
-                    const size_t o = (size_t)base[j] + lane + (size_t)k * kSellC;
-                    cv[j] = col[o];
-                    vv[j] = val[o];
-                }
-            }
+        } else {
 #pragma unroll
             for (int j = 0; j < R; ++j)
-                if (k < len[j])
-                    nv[j] = nv[j] + vv[j] * lm[cv[j]];
+                nv[j] = 0.0;
+            for (int k = 0; k < maxlen; ++k) {
+                // entry k of every row slot: loads first, then the LDS gathers
+                int cv[R];
+                double vv[R];
+#pragma unroll
+                for (int j = 0; j < R; ++j) {
+                    cv[j] = 0;
+                    vv[j] = 0.0;
+                    if (k < len[j]) {
+                        const int o = base[j] + lane + k * kSellC;
+                        cv[j] = col[o];
+                        vv[j] = val[o];
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < R; ++j)
+                    if (k < len[j])
+                        nv[j] = nv[j] + vv[j] * m[cv[j]];
+            }
         }
-        __syncthreads();  // every gather of m done before the next update rewrites it
+        __syncthreads();  // the new scalars visible; every wavefront past its reads of m and part
     }
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-        const int i = threadIdx.x + j * kSmallThreads;
+        const int i = tid + j * kSmallThreads;
         if (i < n) {
             Z[i] = z[j];
             S[i] = s[j];
             P[i] = p[j];
             Rv[i] = r[j];
-            U[i] = u[j];
-            W[i] = w[j];
+            Wv[i] = w[j];
             NVv[i] = nv[j];
-            M[i] = lm[i];
-            X[i] = lx[i];
+            X[i] = x[j];
         }
     }
-    if (threadIdx.x == 0)
-        *st = loc;
+    if (tid == kSmallThreads - 64) {  // the lane that kept the scalars
+        L.loc.alpha = L.scal[0];
+        L.loc.beta = L.scal[1];
+        L.loc.gamma_prev = c.gamma_prev;
+        L.loc.alpha_prev = c.alpha_prev;
+        L.loc.iter = c.iter;
+        L.loc.i_start = c.i_start;
+        L.loc.phase = c.phase;
+        *st = L.loc;
+    }
+}
+
+__global__ __launch_bounds__(kSmallThreads) void k_small_iter(const WorkItem *__restrict__ table,
+                                                              const int *__restrict__ count,
+                                                              const SysDesc *__restrict__ descs, int iters)
+{
+    __shared__ SmallLds L;
+    if ((int)blockIdx.x >= *count)
+        return;
+    const SysDesc &d = descs[table[blockIdx.x].slot];
+    // (with lists of 7 the addresses do not fit the registers beside the vectors)
+    if (d.schunk && d.smaxlen > 0 && d.smaxlen <= 5)
+        small_run<5>(d, iters, L);
+    else
+        small_run<0>(d, iters, L);
 }
 
 }  // namespace ppcg

@@ -139,6 +139,28 @@ def test_classic_pcg_on_lists(gen, prec):
     assert np.array_equal(res[0][0], res[1][0]) and res[0][1:] == res[1][1:]
 
 
+@pytest.mark.parametrize("gen", [lambda: tridiagonal(2, np.full(1, -1.0)), lambda: tridiagonal(63, np.full(62, -1.0)),
+                                 lambda: tridiagonal(1025, np.full(1024, -1.0)), lambda: poisson2d(32),
+                                 lambda: poisson2d(63), lambda: poisson2d(64), lambda: box(15, 16, 17),
+                                 lambda: halves(4000, 2020)])
+def test_one_workgroup_kernel_reads_every_storage_alike(gen):
+    """At most 4,096 rows: the matrix from lists, staged in LDS through the value table, or from memory; 1 to 4 rows
+    per thread, full and ragged wavefronts.  Equal bit for bit, and the oracle's iterates to 1e-10."""
+    A = gen()
+    b = rhs_from_solution(A, xstar_uniform(A.n, 5))
+    k = min(20, A.n - 1)
+    xs = []
+    for flags in (0, ppcg.FLAG_SELL_VALUE_TABLE | ppcg.FLAG_SELL_NO_SHARED_OFFSETS, ppcg.FLAG_SELL_FULL_VALUES):
+        S = Solver(A, fixed_iters=k, spmv_format="sell", flags=flags)
+        x, info = S.solve(dev(b))
+        ref = oracle.pipecg(A, b, fixed_iters=k)
+        assert info["iters"] == ref.iters
+        assert np.linalg.norm(host(x) - ref.x) <= 1e-10 * np.linalg.norm(ref.x)
+        xs.append(host(x))
+        S.close()
+    assert np.array_equal(xs[0], xs[1]) and np.array_equal(xs[0], xs[2])
+
+
 def test_batch_of_list_and_column_systems_equals_solo_bitwise():
     """Both kernels in one batch, twice (captured graphs replayed), with systems that end at different times."""
     mats = [poisson2d(80), shifted(poisson2d(121), 0.3), poisson3d(33), box(31, 17, 20), poisson2d(40)]
