@@ -272,8 +272,9 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_fused(const
             v[3] = v[3] + b[1];
         }
         block_sum<kFusedThreads, kNumPartials>(v, lds);
+        SysState loc;
         if (tid == 0) {
-            SysState loc = *rin;
+            loc = *rin;
             // the update of the previous launch deferred or applied an x-update
             if (!loc.phase) {
                 loc.alpha_x = loc.alpha;
@@ -290,12 +291,13 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_fused(const
             sc.x_finish = loc.done && loc.x_pending;
             if (sc.x_finish)
                 loc.x_pending = 0;
-            if (wi.tile == 0) {
-                d.frec[par ^ 1] = loc;
-                *d.st = loc;
-            }
         }
         __syncthreads();
+        // (behind the barrier, which would wait for these stores)
+        if (tid == 0 && wi.tile == 0) {
+            d.frec[par ^ 1] = loc;
+            *d.st = loc;
+        }
     }
     if (!sc.go) {
         if (sc.x_finish) {

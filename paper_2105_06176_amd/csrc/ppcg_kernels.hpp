@@ -118,11 +118,99 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Sum NV values over the workgroup in a fixed order; result valid in thread 0.
-template <int NT, int NV>
-__device__ __forceinline__ void block_sum(double (&v)[NV], double *lds /* [NT/64 * NV] */)
+// a + b after the upper half (SWAP 32) or the odd rows of 16 (SWAP 16) of a
+// changed places with the lower half or the even rows of b: lanes of the
+// first kind hold a's sum with its partner lane, the others b's.
+template <int SWAP>
+__device__ __forceinline__ double swap_add(double a, double b)
+{
+    const unsigned long long x = (unsigned long long)__double_as_longlong(a);
+    const unsigned long long y = (unsigned long long)__double_as_longlong(b);
+    uvec2 lo, hi;
+    if constexpr (SWAP == 32) {
+        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+        lo = uvec2{l[0], l[1]};
+        hi = uvec2{h[0], h[1]};
+    } else {
+        const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+        lo = uvec2{l[0], l[1]};
+        hi = uvec2{h[0], h[1]};
+    }
+    return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
+           __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+
+// Sum over each row of 16 lanes, in every lane of the row.
+__device__ __forceinline__ double row_sum(double v)
+{
+    v = v + dpp_f64<0x128>(v);  // row_ror:8
+    v = v + dpp_f64<0x124>(v);  // row_ror:4
+    v = v + dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
+    v = v + dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
+    return v;
+}
+
+// The value of lane j (uniform) in every lane.
+__device__ __forceinline__ double readlane_f64(double v, int j)
+{
+    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, j);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), j);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// The wavefront's sums of four values at once: lane l ends with the sum of
+// v[l / 16].  Two exchanges halve the values each lane carries, where four
+// separate butterflies would add every value in every lane at every step
+// (7 additions and 14 moves instead of 24 and 48).  The pairs are those of
+// wave_sum, so each sum is bit for bit wave_sum's.
+__device__ __forceinline__ double wave_sum4(const double (&v)[4])
+{
+    const double a = swap_add<32>(v[0], v[2]), b = swap_add<32>(v[1], v[3]);
+    return row_sum(swap_add<16>(a, b));
+}
+
+// Four values over the wavefronts' sums part[k * W + wavefront], in wavefront
+// order: lane l of the calling wavefront ends with value l & 3.
+template <int W>
+__device__ __forceinline__ double waves_sum4(const double *part)
+{
+    const double *q = part + (threadIdx.x & 3) * W;
+    double t = q[0];
+#pragma unroll
+    for (int w = 1; w < W; ++w)
+        t = t + q[w];
+    return t;
+}
+
+// Four values over the workgroup: lane l of wavefront 0 ends with value l & 3.
+template <int NT>
+__device__ __forceinline__ double block_sum4(const double (&v)[4], double *lds /* [NT/64 * 4] */)
 {
     constexpr int W = NT / 64;
+    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const double ws = wave_sum4(v);
+    if ((lane & 15) == 0)
+        lds[(lane >> 4) * W + wid] = ws;
+    __syncthreads();
+    return wid == 0 ? waves_sum4<W>(lds) : 0.0;
+}
+
+// Sum NV values over the workgroup in a fixed order (wave_sum, then the
+// wavefronts in order); result valid in thread 0.
+template <int NT, int NV>
+__device__ __forceinline__ void block_sum(double (&v)[NV], double *lds /* [NT/64 * NV], NV = 3: as 4 */)
+{
+    constexpr int W = NT / 64;
+    if constexpr (NV == 3 || NV == 4) {
+        const double t = block_sum4<NT>({v[0], v[1], v[2], NV == 4 ? v[NV - 1] : 0.0}, lds);
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            v[k] = readlane_f64(t, k);
+        return;
+    }
     const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
     for (int k = 0; k < NV; ++k)
@@ -256,6 +344,89 @@ __device__ inline void scalar_update(const SysDesc &d, SysState *st, const doubl
     st->beta = beta;
     st->gamma_prev = g;
     st->alpha_prev = alpha;
+}
+
+// The scalar record of a launch in LDS: read by 32 threads, updated by thread
+// 0, written by 32 threads of tile 0.
+constexpr int kRecWords = sizeof(SysState) / sizeof(int);
+static_assert(kRecWords == 32, "one word per thread");
+__device__ __forceinline__ void rec_load(SysState *lds, const SysState *rec)
+{
+    if (threadIdx.x < kRecWords)
+        ((int *)lds)[threadIdx.x] = as_global((const int *)rec)[threadIdx.x];
+}
+__device__ __forceinline__ void rec_store(SysState *rec, const SysState *lds)
+{
+    if (threadIdx.x < kRecWords)
+        as_global((int *)rec)[threadIdx.x] = ((const int *)lds)[threadIdx.x];
+}
+
+// scalar_update for FP64 PIPECG with what it reads in registers and limit =
+// tol (STOP_ABS) or tol ||b||.  rec: a copy of the old record in LDS, which
+// becomes the new one.  (scalar_update on a record in LDS pays a round trip
+// for every field in the chain that the workgroup waits for; on a local copy
+// of the whole record the compiler puts one into LDS for every thread.)
+struct ScalarIn {
+    double gamma_prev, alpha_prev, limit;
+    int iter, i_start, phase;
+};
+struct ScalarOut {
+    double alpha, beta;
+    int go, iter, i_start;
+};
+
+__device__ __forceinline__ double stop_limit(const SysDesc &d, double bnorm2)
+{
+    return d.stop == STOP_ABS ? d.tol : d.tol * sqrt(bnorm2);
+}
+
+__device__ __forceinline__ ScalarOut pipecg_scalars(const SysDesc &d, const ScalarIn &c,
+                                                    const double (&v)[kNumPartials], SysState *rec)
+{
+    ScalarOut o;
+    o.iter = c.iter + (c.phase ? 0 : 1);
+    o.i_start = c.i_start + (c.phase ? 0 : 1);
+    const double g = v[0], dl = v[1];
+    bool conv;
+    if (d.fixed > 0)
+        conv = o.iter >= d.fixed || g == 0.0;
+    else if (d.stop == STOP_ABS)
+        conv = sqrt(v[2]) < c.limit;
+    else
+        conv = sqrt(v[3]) <= c.limit;
+    o.beta = 0.0;
+    double denom = dl;
+    if (o.i_start > 0) {
+        o.beta = g / c.gamma_prev;
+        denom = dl - o.beta * g / c.alpha_prev;
+    }
+    o.alpha = g / denom;
+    int status = -1;
+    if (conv)
+        status = ST_OK;
+    else if (d.fixed <= 0 && o.iter >= d.maxit)
+        status = ST_NOT_CONVERGED;
+    else if (!(g > 0.0) || !(denom > 0.0) || !isfinite(o.alpha) || !isfinite(o.beta))
+        status = ST_BREAKDOWN;
+    o.go = status < 0;
+    rec->phase = 0;
+    rec->iter = o.iter;
+    rec->i_start = o.i_start;
+    rec->gamma_prev2 = c.gamma_prev;
+    rec->gamma = g;
+    rec->delta = dl;
+    rec->uu = v[2];
+    rec->rr = v[3];
+    if (o.go) {
+        rec->alpha = o.alpha;
+        rec->beta = o.beta;
+        rec->gamma_prev = g;
+        rec->alpha_prev = o.alpha;
+    } else {
+        rec->done = 1;
+        rec->status = status;
+    }
+    return o;
 }
 
 // Scalars after a residual replacement.  r, u, w, m, n were recomputed from

@@ -438,29 +438,13 @@ __device__ inline void pcg_scalar_update(const SysDesc &d, SysState *st, double 
     st->beta = kind == PCG_START || st->i_start == 0 ? 0.0 : g / st->gamma_prev;
 }
 
-// The scalar record of a launch in LDS: read by 32 threads, updated by thread
-// 0, written by 32 threads of tile 0.  (A record in thread 0's registers is
-// put into LDS by the compiler anyway, one copy per thread.)
-constexpr int kRecWords = sizeof(SysState) / sizeof(int);
-static_assert(kRecWords == 32, "one word per thread");
-__device__ __forceinline__ void pcg_rec_load(SysState *lds, const SysState *rec)
-{
-    if (threadIdx.x < kRecWords)
-        ((int *)lds)[threadIdx.x] = as_global((const int *)rec)[threadIdx.x];
-}
-__device__ __forceinline__ void pcg_rec_store(SysState *rec, const SysState *lds)
-{
-    if (threadIdx.x < kRecWords)
-        as_global((int *)rec)[threadIdx.x] = ((const int *)lds)[threadIdx.x];
-}
-
 // first: the first iteration of a chunk, from the canonical state.
 template <typename T>
 __global__ __launch_bounds__(kSpmvThreads, 8) void k_pcg_spmv(const WorkItem *__restrict__ table,
                                                               const int *__restrict__ count,
                                                               const SysDesc *__restrict__ descs, int remap, int first)
 {
-    __shared__ double lds[kSpmvThreads / 64 * 3];
+    __shared__ double lds[kSpmvThreads / 64 * 4];
     __shared__ SysState loc;
     // Graphs bake a grid that may exceed the live table: blocks past it exit,
     // and the XCD-aware order is taken over the live items only, so that
@@ -472,12 +456,12 @@ __global__ __launch_bounds__(kSpmvThreads, 8) void k_pcg_spmv(const WorkItem *__
     const WorkItem wi = table[pos];
     const SysDesc &d = descs[wi.slot];
     const SysState *rin = first ? d.st : d.prs + 1;
-    pcg_rec_load(&loc, rin);
+    rec_load(&loc, rin);
     double v[3];
     pcg_first_record<3>(d, 1, v);
     if (as_constant(rin)->done) {  // k_pcg_vma reads the stop from the other record
         if (wi.tile == 0)  // (each thread stores the word it loaded)
-            pcg_rec_store(d.prs, &loc);
+            rec_store(d.prs, &loc);
         return;
     }
     if (!first) {
@@ -487,7 +471,7 @@ __global__ __launch_bounds__(kSpmvThreads, 8) void k_pcg_spmv(const WorkItem *__
     }
     __syncthreads();
     if (wi.tile == 0)
-        pcg_rec_store(d.prs, &loc);
+        rec_store(d.prs, &loc);
     if (loc.done)
         return;
     const T beta = (T)loc.beta;
@@ -524,7 +508,7 @@ __global__ __launch_bounds__(kPcgVmaThreads) void k_pcg_vma(const WorkItem *__re
                                                             const SysDesc *__restrict__ descs, int remap)
 {
     using V2 = typename Vec2<T>::type;
-    __shared__ double lds[kPcgVmaThreads / 64 * 3];
+    __shared__ double lds[kPcgVmaThreads / 64 * 4];
     __shared__ SysState loc;
     const int live = *count;
     if ((int)blockIdx.x >= live)
@@ -534,12 +518,12 @@ __global__ __launch_bounds__(kPcgVmaThreads) void k_pcg_vma(const WorkItem *__re
     const SysDesc &d = descs[wi.slot];
     const SysState *rin = d.prs;
     const auto *rc = as_constant(rin);
-    pcg_rec_load(&loc, rin);
+    rec_load(&loc, rin);
     double v[1];
     pcg_first_record<1>(d, 0, v);
     if (rc->done) {
         if (wi.tile == 0)
-            pcg_rec_store(d.prs + 1, &loc);
+            rec_store(d.prs + 1, &loc);
         return;
     }
     const int n = d.n, row0 = wi.tile * d.frows, row1 = min(row0 + d.frows, n);
@@ -576,7 +560,7 @@ __global__ __launch_bounds__(kPcgVmaThreads) void k_pcg_vma(const WorkItem *__re
         __syncthreads();
     }
     if (wi.tile == 0)
-        pcg_rec_store(d.prs + 1, &loc);
+        rec_store(d.prs + 1, &loc);
     if (loc.done)
         return;
     const T alpha = (T)loc.alpha;
@@ -686,7 +670,7 @@ __global__ __launch_bounds__(kPcgRedThreads) void k_pcg_update(const WorkItem *_
     SysState *st = d.st;
     if constexpr (KIND == PCG_ITER) {
         __shared__ SysState loc;
-        pcg_rec_load(&loc, d.prs + 1);
+        rec_load(&loc, d.prs + 1);
         double v[3];
         pcg_first_record<3>(d, 1, v);
         if (!as_constant((const SysState *)d.prs)[1].done) {
@@ -695,7 +679,7 @@ __global__ __launch_bounds__(kPcgRedThreads) void k_pcg_update(const WorkItem *_
                 pcg_scalar_update(d, &loc, v[0], v[1], v[2], KIND);
         }
         __syncthreads();
-        pcg_rec_store(st, &loc);
+        rec_store(st, &loc);
     } else {
         double v[kNumPartials];
         pcg_reduce<kNumPartials>(d, 1, v, lds);

@@ -46,60 +46,6 @@ constexpr int kSmallWaves = kSmallThreads / 64;
 static_assert(kSmallMaxRows <= 32768, "column offsets from the row fit 16 bits");
 static_assert(PPCG_SMALL_MAX_ROWS <= kSmallMaxRows, "small systems must fit the register-resident kernel");
 
-// a + b after the upper half (SWAP 32) or the odd rows of 16 (SWAP 16) of a
-// changed places with the lower half or the even rows of b: lanes of the
-// first kind hold a's sum with its partner lane, the others b's.
-template <int SWAP>
-__device__ __forceinline__ double swap_add(double a, double b)
-{
-    const unsigned long long x = (unsigned long long)__double_as_longlong(a);
-    const unsigned long long y = (unsigned long long)__double_as_longlong(b);
-    uvec2 lo, hi;
-    if constexpr (SWAP == 32) {
-        const auto l = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-        lo = uvec2{l[0], l[1]};
-        hi = uvec2{h[0], h[1]};
-    } else {
-        const auto l = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)y, false, false);
-        const auto h = __builtin_amdgcn_permlane16_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
-        lo = uvec2{l[0], l[1]};
-        hi = uvec2{h[0], h[1]};
-    }
-    return __longlong_as_double((long long)(((unsigned long long)hi[0] << 32) | lo[0])) +
-           __longlong_as_double((long long)(((unsigned long long)hi[1] << 32) | lo[1]));
-}
-
-// Sum over each row of 16 lanes, in every lane of the row.
-__device__ __forceinline__ double row_sum(double v)
-{
-    v = v + dpp_f64<0x128>(v);  // row_ror:8
-    v = v + dpp_f64<0x124>(v);  // row_ror:4
-    v = v + dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
-    v = v + dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
-    return v;
-}
-
-// The value of lane j (uniform) in every lane.
-__device__ __forceinline__ double readlane_f64(double v, int j)
-{
-    const unsigned long long b = (unsigned long long)__double_as_longlong(v);
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, j);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), j);
-    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
-// The wavefront's sums of four values at once: lane l ends with the sum of
-// v[l / 16].  Two exchanges halve the values each lane carries, where four
-// separate butterflies would add every value in every lane at every step
-// (7 additions and 14 moves instead of 24 and 48).  The pairs are those of
-// wave_sum, so each sum is bit for bit wave_sum's.
-__device__ __forceinline__ double wave_sum4(const double (&v)[kNumPartials])
-{
-    const double a = swap_add<32>(v[0], v[2]), b = swap_add<32>(v[1], v[3]);
-    return row_sum(swap_add<16>(a, b));
-}
-
 // Entries k0 .. k0 + L - 1 of a row from the lists: lane's row at byte rowb
 // of the LDS vector m, absent entries at byte zero.
 template <int L>
@@ -141,61 +87,6 @@ struct SmallLds {
     unsigned char lvi[kSmallLdsEntries];  // and value index
     double ltab[kMaxValueTable];          // the value table
 };
-
-// scalar_update (ppcg_kernels.hpp) for FP64 PIPECG with what it reads kept in
-// registers: through the record in LDS every field costs a round trip of the
-// chain that all wavefronts wait for.
-struct SmallScalars {
-    double gamma_prev, alpha_prev, limit;  // limit: of the stopping quantity
-    int iter, i_start, phase;
-};
-
-__device__ __forceinline__ void small_scalars(const SysDesc &d, SmallScalars &c, const double (&v)[kNumPartials],
-                                              SmallLds &L)
-{
-    if (c.phase) {
-        c.phase = 0;
-    } else {
-        c.iter += 1;
-        c.i_start += 1;
-    }
-    const double g = v[0], dl = v[1];
-    L.loc.gamma_prev2 = c.gamma_prev;
-    L.loc.gamma = g;
-    L.loc.delta = dl;
-    L.loc.uu = v[2];
-    L.loc.rr = v[3];
-    bool conv;
-    if (d.fixed > 0)
-        conv = c.iter >= d.fixed || g == 0.0;
-    else if (d.stop == STOP_ABS)
-        conv = sqrt(v[2]) < c.limit;
-    else
-        conv = sqrt(v[3]) <= c.limit;
-    int status = -1;
-    double beta = 0.0, denom = dl;
-    if (c.i_start > 0) {
-        beta = g / c.gamma_prev;
-        denom = dl - beta * g / c.alpha_prev;
-    }
-    const double alpha = g / denom;
-    if (conv)
-        status = ST_OK;
-    else if (d.fixed <= 0 && c.iter >= d.maxit)
-        status = ST_NOT_CONVERGED;
-    else if (!(g > 0.0) || !(denom > 0.0) || !isfinite(alpha) || !isfinite(beta))
-        status = ST_BREAKDOWN;
-    if (status >= 0) {
-        L.loc.done = 1;
-        L.loc.status = status;
-        L.stop = 1;
-        return;
-    }
-    L.scal[0] = alpha;
-    L.scal[1] = beta;
-    c.gamma_prev = g;
-    c.alpha_prev = alpha;
-}
 
 // E > 0: chunk lists of at most E entries.  The LDS address of every entry of
 // the thread's rows is formed once (two 16-bit addresses per register), so an
@@ -242,15 +133,9 @@ __device__ __forceinline__ void small_run(const SysDesc &d, int iters, SmallLds 
         L.scal[1] = st->beta;
         m[kSmallMaxRows] = 0.0;
     }
-    SmallScalars c{};
-    if (wave == kSmallWaves - 1) {
-        c.gamma_prev = st->gamma_prev;
-        c.alpha_prev = st->alpha_prev;
-        c.limit = d.stop == STOP_ABS ? d.tol : d.tol * sqrt(st->bnorm2);
-        c.iter = st->iter;
-        c.i_start = st->i_start;
-        c.phase = st->phase;
-    }
+    ScalarIn c{};
+    if (wave == kSmallWaves - 1)
+        c = {st->gamma_prev, st->alpha_prev, stop_limit(d, st->bnorm2), st->iter, st->i_start, st->phase};
     // chunk j of this wavefront: rows wave * 64 + j * kSmallThreads + lane
     const bool lists = E > 0 || d.schunk != nullptr;
     int base[R], len[R], msk[R], maxlen = 0;
@@ -327,15 +212,14 @@ __device__ __forceinline__ void small_run(const SysDesc &d, int iters, SmallLds 
             L.part[(lane >> 4) * kSmallWaves + wave] = ws;
         __syncthreads();  // m and the wavefronts' sums complete
         if (wave == kSmallWaves - 1) {
-            // lane k < 4: value k, the wavefronts in order
-            const double *q = L.part + (lane & 3) * kSmallWaves;
-            double t = q[0];
-#pragma unroll
-            for (int k = 1; k < kSmallWaves; ++k)
-                t = t + q[k];
+            const double t = waves_sum4<kSmallWaves>(L.part);
             const double v[kNumPartials] = {readlane_f64(t, 0), readlane_f64(t, 1), readlane_f64(t, 2),
                                             readlane_f64(t, 3)};
-            small_scalars(d, c, v, L);
+            const ScalarOut o = pipecg_scalars(d, c, v, &L.loc);
+            L.scal[0] = o.alpha;
+            L.scal[1] = o.beta;
+            L.stop = !o.go;
+            c = {v[0], o.alpha, c.limit, o.iter, o.i_start, 0};
         }
         // n = A m (stored entries of a system with at most kSmallMaxRows rows
         // fit 32 bits)
@@ -422,16 +306,8 @@ __device__ __forceinline__ void small_run(const SysDesc &d, int iters, SmallLds 
             X[i] = x[j];
         }
     }
-    if (tid == kSmallThreads - 64) {  // the lane that kept the scalars
-        L.loc.alpha = L.scal[0];
-        L.loc.beta = L.scal[1];
-        L.loc.gamma_prev = c.gamma_prev;
-        L.loc.alpha_prev = c.alpha_prev;
-        L.loc.iter = c.iter;
-        L.loc.i_start = c.i_start;
-        L.loc.phase = c.phase;
-        *st = L.loc;
-    }
+    if (tid < (int)(sizeof(SysState) / sizeof(int)))
+        as_global((int *)st)[tid] = ((const int *)&L.loc)[tid];
 }
 
 __global__ __launch_bounds__(kSmallThreads) void k_small_iter(const WorkItem *__restrict__ table,

@@ -136,9 +136,8 @@ __global__ __launch_bounds__(64) void k_st_verify(int nchunks, const int64_t *__
 
 // ---------------------------------------------------------------- iteration
 struct StScalars {
-    double alpha, beta;
     double hist[2 * kStDefer];  // alpha, beta of the updates since the last full ring
-    int go;
+    SysState rec;
 };
 
 // The handle's vectors lie in one allocation at a fixed distance: one buffer
@@ -196,6 +195,7 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
         pa1 = PR[2 * (tid + kFusedThreads)];
         pb1 = PR[2 * (tid + kFusedThreads) + 1];
     }
+    rec_load(&sc.rec, d.frec + par);
     double hist = 0.0;
     if (tid < 2 * kStDefer)
         hist = as_global(d.shist)[par * kStHist + tid];
@@ -203,8 +203,8 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
     __asm__ volatile("" ::: "memory");  // the loads above stay above the check
     if (rin->done) {
         // publish the stop in the other slot too (see k_fused)
-        if (wi.tile == 0 && threadIdx.x == 0)
-            d.frec[par ^ 1] = *(const SysState *)rin;
+        if (wi.tile == 0)  // (each thread stores the word it loaded)
+            rec_store(d.frec + (par ^ 1), &sc.rec);
         return;
     }
     // Vectors, by their byte distance from x.  w is double buffered by parity
@@ -216,11 +216,16 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
     // The update number i of a start.  With the ring of residuals r, q, nv, m
     // it reads r_i from buffer i mod kStDefer and writes r_{i+1} to the next.
     const bool ring = d.sring != 0;
+    const ScalarIn c = {rin->gamma_prev, rin->alpha_prev, stop_limit(d, rin->bnorm2),
+                        rin->iter, rin->i_start, rin->phase};
     const int at = (rin->i_start + (rin->phase ? 0 : 1)) & (ring ? kStDefer - 1 : 1);
     static_assert(kStDefer == 4, "the ring is r, q, nv, m");
     auto buf = [vs](int k) { return (k == 0 ? 1 : k == 1 ? 7 : k == 2 ? 5 : 4) * vs; };
     const int oR = buf(ring ? at : 0), oRo = buf(ring ? (at + 1) & (kStDefer - 1) : 0);
-    // 0. This thread's first row of n = A m.
+    // 0. This thread's first row: the update's operands and n = A m.  A lane
+    // past the last row reads zeros and its stores are dropped.
+    int ib = row0 + tid < n ? (row0 + tid) * 8 : 0x7ffffff0;
+    double w = st_load(wb, ib), s = st_vec(V, ib, oS), z = st_vec(V, ib, oZ), r = st_vec(V, ib, oR);
     double nv = 0.0;
     if (some)
         nv = st_row<true>(d, ch, wb, (row0 + tid) * 8, d0);
@@ -249,20 +254,16 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
         if (tid < 2 * kStDefer)
             sc.hist[tid] = hist;
         block_sum<kFusedThreads, kNumPartials>(v, lds);
-        if (tid == 0) {
-            SysState loc = *(const SysState *)rin;
-            scalar_update<kNumPartials>(d, &loc, v);
-            sc.alpha = loc.alpha;
-            sc.beta = loc.beta;
-            sc.go = !loc.done;
-            if (wi.tile == 0) {
-                d.frec[par ^ 1] = loc;
-                *d.st = loc;
-            }
-        }
+        if (tid == 0)
+            pipecg_scalars(d, c, v, &sc.rec);
         __syncthreads();
+        // (behind the barrier, which would wait for these stores)
+        if (wi.tile == 0) {
+            rec_store(d.frec + (par ^ 1), &sc.rec);
+            rec_store(d.st, &sc.rec);
+        }
     }
-    if (!sc.go) {
+    if (sc.rec.done) {
         // the updates of x (with the ring, of p and x) deferred so far, so
         // that x is complete when the host reads the state
         if (at > 0)
@@ -282,7 +283,7 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
             }
         return;
     }
-    const double sa = sc.alpha, sb = sc.beta;
+    const double sa = sc.rec.alpha, sb = sc.rec.beta;
     if (wi.tile == 0 && tid < 2 * kStDefer)
         as_global(d.shist)[(par ^ 1) * kStHist + tid] =
             (tid & (kStDefer - 1)) != at ? hist : tid < kStDefer ? sa : sb;
@@ -294,10 +295,12 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
         const int i = row0 + k * kFusedThreads + tid;
         if (row0 + k * kFusedThreads + wave * kSellC >= n)
             break;  // uniform per wavefront
-        // a lane past the last row reads zeros and its stores are dropped
-        const int ib = i < n ? i * 8 : 0x7ffffff0;
-        double w = st_load(wb, ib), s = st_vec(V, ib, oS), z = st_vec(V, ib, oZ), r = st_vec(V, ib, oR);
         if (k > 0) {
+            ib = i < n ? i * 8 : 0x7ffffff0;
+            w = st_load(wb, ib);
+            s = st_vec(V, ib, oS);
+            z = st_vec(V, ib, oZ);
+            r = st_vec(V, ib, oR);
             ch = CH[c0 + k * (kFusedThreads / kSellC)];
             nv = st_row<true>(d, ch, wb, i * 8, d0);
         }
@@ -339,12 +342,9 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
         st_put(V, ib, oWo, w);
         st_put(V, ib, oZ, z);
     }
-    block_sum<kFusedThreads, kNumPartials>(acc, lds);
-    if (tid == 0) {
-        PPCG_AS1 dvec2 *out = (PPCG_AS1 dvec2 *)as_global(d.fpart + ((size_t)(par ^ 1) * d.nftiles + wi.tile) * 4);
-        out[0] = dvec2{acc[0], acc[1]};
-        out[1] = dvec2{acc[2], acc[3]};
-    }
+    const double t = block_sum4<kFusedThreads>(acc, lds);
+    if (tid < kNumPartials)
+        as_global(d.fpart)[((size_t)(par ^ 1) * d.nftiles + wi.tile) * 4 + tid] = t;
 }
 
 }  // namespace ppcg
