@@ -258,6 +258,7 @@ struct Group {
         hipGraphExec_t exec = nullptr;
     };
     std::map<int, CapturedGraph> graphs;
+    SysDesc solo{};  // one-system engines, k_stencil: the descriptor baked into the graphs (options cleared)
     int g_grid = 0;
 };
 
@@ -401,9 +402,10 @@ void launch_pipecg_iter(hipStream_t s, const WorkItem *tab, const int *cnt, cons
 void launch_pipecg_init_fused(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid,
                               bool x_zero = false);
 // K launches of the single-launch form over a table of fused tiles (K even),
-// preceded by k_fused_begin; stencil: k_stencil instead of k_fused.
+// preceded by k_fused_begin; stencil: k_stencil instead of k_fused; solo: the
+// only system's descriptor, when the table holds its tiles in order (or NULL).
 void launch_fused_chunk(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int iters,
-                        bool stencil);
+                        bool stencil, const SysDesc *solo);
 // Allocate the single-launch form's buffers of a handle (once).
 ppcg_status ensure_fused(ppcg_handle *h);
 // Fused tiles of a handle's system (fused_tile_rows(n, cus) rows each).

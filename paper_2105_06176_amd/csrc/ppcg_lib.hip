@@ -1777,20 +1777,22 @@ void launch_pipecg_init_fused(hipStream_t s, const WorkItem *tab, const int *cnt
 
 // One launch of the single-launch form with parity i & 1.
 static void launch_fused(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int i,
-                         bool stencil)
+                         bool stencil, const SysDesc *solo)
 {
-    if (stencil)
-        k_stencil<<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1);
+    if (stencil && solo)
+        k_stencil<true><<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1, *solo);
+    else if (stencil)
+        k_stencil<false><<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1, SysDesc{});
     else
         k_fused<<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1);
 }
 
 void launch_fused_chunk(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int iters,
-                        bool stencil)
+                        bool stencil, const SysDesc *solo)
 {
     k_fused_begin<<<grid, 64, 0, s>>>(tab, cnt, dd);
     for (int i = 0; i < iters; ++i)
-        launch_fused(s, tab, cnt, dd, grid, i, stencil);
+        launch_fused(s, tab, cnt, dd, grid, i, stencil, solo);
 }
 
 void launch_true_resid(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid)
@@ -1908,6 +1910,17 @@ ppcg_status Engine::ensure_graph(Group &g, int iters, hipGraphExec_t *exec)
     if (g.g_grid < need || g.g_grid > std::max(need * 4, 64) ||
         (g.pcg && (g.g_sys_grid < need_sys || g.g_sys_grid > std::max(need_sys * 4, 16))))
         drop_graphs(g);
+    // an engine of one system: its graphs hold the descriptor, without the
+    // options
+    const bool solo = g.stencil && g.cap_sys == 1;
+    if (solo) {
+        SysDesc own = g.desc_h[0];
+        own.tol = 0.0;
+        own.stop = own.maxit = own.fixed = 0;
+        if (memcmp(&own, &g.solo, sizeof own) != 0)
+            drop_graphs(g);
+        memcpy(&g.solo, &own, sizeof own);
+    }
     auto it = g.graphs.find(iters);
     if (it != g.graphs.end()) {
         *exec = it->second.exec;
@@ -1920,7 +1933,8 @@ ppcg_status Engine::ensure_graph(Group &g, int iters, hipGraphExec_t *exec)
     Group::CapturedGraph cg;
     PPCG_HIP(hipStreamBeginCapture(stream_, hipStreamCaptureModeThreadLocal));
     if (g.fused)
-        launch_fused_chunk(stream_, g.table_d, g.count_d, g.desc_d, grid, iters, g.stencil);
+        launch_fused_chunk(stream_, g.table_d, g.count_d, g.desc_d, grid, iters, g.stencil,
+                           solo ? &g.solo : nullptr);
     else
         launch_iters(stream_, g, grid, remap, iters);
     hipError_t e = hipStreamEndCapture(stream_, &cg.graph);
@@ -3258,13 +3272,19 @@ ppcg_status ppcg_time_kernels(ppcg_handle *h, const double *b, int32_t iters, do
         launch_pipecg_init_fused(s, tab, cnt, dd, grid);
         k_fused_begin<<<fgrid, 64, 0, s>>>(tab, cnt + 1, dd);
         const bool stencil = h->schunk != nullptr;
-        launch_fused(s, tab, cnt + 1, dd, fgrid, 0, stencil);
+        SysDesc own;
+        PPCG_TRY(fill_desc(h, PREC_F64, h->plain_st, &own, 0.0, INT_MAX, INT_MAX, STOP_REL));
+        launch_fused(s, tab, cnt + 1, dd, fgrid, 0, stencil, &own);
         for (auto &e : ev)
             PPCG_HIP_CLEAN(hipEventCreate(&e), clean());
-        for (int i = 1; i <= iters; ++i)
-            hipExtLaunchKernelGGL(stencil ? k_stencil : k_fused, dim3(fgrid), dim3(kFusedThreads), 0, s,
-                                  ev[4 * (i - 1)], ev[4 * (i - 1) + 1], 0, tab, cnt + 1, dd, (int)PPCG_FUSED_REMAP,
-                                  i & 1);
+        for (int i = 1; i <= iters; ++i) {
+            if (stencil)
+                hipExtLaunchKernelGGL(k_stencil<true>, dim3(fgrid), dim3(kFusedThreads), 0, s, ev[4 * (i - 1)],
+                                      ev[4 * (i - 1) + 1], 0, tab, cnt + 1, dd, (int)PPCG_FUSED_REMAP, i & 1, own);
+            else
+                hipExtLaunchKernelGGL(k_fused, dim3(fgrid), dim3(kFusedThreads), 0, s, ev[4 * (i - 1)],
+                                      ev[4 * (i - 1) + 1], 0, tab, cnt + 1, dd, (int)PPCG_FUSED_REMAP, i & 1);
+        }
         PPCG_HIP_CLEAN(hipGetLastError(), clean());
         PPCG_HIP_CLEAN(hipStreamSynchronize(s), clean());
         double tf = 0;

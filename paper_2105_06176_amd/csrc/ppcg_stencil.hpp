@@ -157,19 +157,25 @@ __device__ __forceinline__ void st_put(StBuf v, int byte, int vec, double x)
 // the diagonal is constant.  The registers stay at 61 (8 wavefronts per
 // SIMD): local copies that the compiler cannot split went to LDS, with
 // 10 us per launch.
+//
+// SOLO: the table is one system's tiles in order, and the descriptor comes
+// with the kernel's arguments (the options in it do not: they are read from
+// descs[0], so that a captured launch stays valid when they change).  It saves
+// two dependent loads at the start of every launch.
+template <bool SOLO>
 __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(const WorkItem *__restrict__ table,
                                                                              const int *__restrict__ count,
                                                                              const SysDesc *__restrict__ descs,
-                                                                             int remap, int par)
+                                                                             int remap, int par, const SysDesc own)
 {
     __shared__ double lds[kFusedThreads / 64 * kNumPartials];
     __shared__ StScalars sc;
-    const int live = *count;
+    const int live = SOLO ? own.nftiles : *count;
     if ((int)blockIdx.x >= live)
         return;
     const int pos = remap ? xcd_remap(blockIdx.x, live) : (int)blockIdx.x;
-    const WorkItem wi = table[pos];
-    const SysDesc &d = descs[wi.slot];
+    const WorkItem wi = SOLO ? WorkItem{0, pos} : table[pos];
+    const SysDesc &opt = descs[wi.slot], &d = SOLO ? own : opt;
     const int R = d.frows / kFusedThreads;  // rows per thread, 1 .. kFusedRowsPerThread
     // The record and the lists are the same for the workgroup or the
     // wavefront and not written by this launch: scalar loads.
@@ -216,7 +222,7 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
     // The update number i of a start.  With the ring of residuals r, q, nv, m
     // it reads r_i from buffer i mod kStDefer and writes r_{i+1} to the next.
     const bool ring = d.sring != 0;
-    const ScalarIn c = {rin->gamma_prev, rin->alpha_prev, stop_limit(d, rin->bnorm2),
+    const ScalarIn c = {rin->gamma_prev, rin->alpha_prev, stop_limit(opt, rin->bnorm2),
                         rin->iter, rin->i_start, rin->phase};
     const int at = (rin->i_start + (rin->phase ? 0 : 1)) & (ring ? kStDefer - 1 : 1);
     static_assert(kStDefer == 4, "the ring is r, q, nv, m");
@@ -255,7 +261,7 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
             sc.hist[tid] = hist;
         block_sum<kFusedThreads, kNumPartials>(v, lds);
         if (tid == 0)
-            pipecg_scalars(d, c, v, &sc.rec);
+            pipecg_scalars(opt, c, v, &sc.rec);
         __syncthreads();
         // (behind the barrier, which would wait for these stores)
         if (wi.tile == 0) {
