@@ -1976,9 +1976,13 @@ int iters_needed(const SysDesc &d, const SysState &st, double rate, bool polled,
     return std::max(1, std::min(rem, max_iters));
 }
 
-void note_progress(const SysDesc &d, const SysState &st, double *last_norm, int *last_iter, double *rate)
+void note_progress(const SysDesc &d, const SysState &st, double *last_norm, int *last_iter, double *rate, bool from_b)
 {
     const double cur = d.stop == STOP_ABS ? std::sqrt(st.uu) : std::sqrt(st.rr);
+    if (*last_norm < 0.0 && from_b && d.stop == STOP_REL) {
+        *last_norm = std::sqrt(st.bnorm2);
+        *last_iter = 0;
+    }
     if (*last_norm > 0 && st.iter > *last_iter)
         *rate = std::pow(cur / *last_norm, 1.0 / (st.iter - *last_iter));
     *last_norm = cur;
@@ -1994,11 +1998,6 @@ int Engine::chunk_iters(const Group &g, int max_iters)
         want = std::max(want, iters_needed(g.desc_h[pslot(j)], g.st_h[pslot(j)], j.rate, j.last_norm >= 0,
                                            max_iters, g.pcg));
     }
-    // The single-launch form: its first launch after an initialisation does
-    // no update, so k updates take k + 1 launches, and chunks hold an even
-    // number of launches (the parity of m, partials and state returns to 0).
-    if (g.fused)
-        want = std::max(2, std::min(want + 1, std::max(max_iters, 2)));
     int k = 1;
     while (k * 2 <= want)
         k *= 2;
@@ -2018,11 +2017,36 @@ std::vector<int> Engine::chunk_plan(const Group &g, int max_iters, bool *covers)
             all_fixed = false;
         want = std::max(want, iters_needed(d, g.st_h[pslot(j)], j.rate, j.last_norm >= 0, INT_MAX / 4, g.pcg));
     }
-    if (!all_fixed || g.pcg)
-        return {chunk_iters(g, max_iters)};
     int cap = 1;
     while (cap * 2 <= max_iters)
         cap *= 2;
+    if (!all_fixed || g.pcg) {
+        if (g.fused)
+            cap = std::max(cap, 2);  // an even number of launches: the parity of m, partials and state returns to 0
+        bool first = true;
+        int need = 1;
+        double bytes = 0.0;
+        for (const Job &j : jobs_) {
+            if (j.finished || j.stage != JS_ITER || &pgroup(j) != &g)
+                continue;
+            const SysDesc &d = g.desc_h[pslot(j)];
+            bytes += j.iter_bytes;
+            if (j.last_norm >= 0.0 || d.fixed > 0)
+                first = false;
+            need = std::max(need, iters_needed(d, g.st_h[pslot(j)], j.rate, j.last_norm >= 0, cap, g.pcg));
+        }
+        if (first && bytes >= kFirstChunkBytes)
+            need = std::min(need, kFirstChunk - 1);
+        // + 1: the single-launch form's first launch does no update
+        need = std::min(cap, (need + kChunkStep) / kChunkStep * kChunkStep);
+        std::vector<int> plan;
+        for (int c = cap; need > 0; c /= 2)
+            if (c <= need) {
+                plan.push_back(c);
+                need -= c;
+            }
+        return plan;
+    }
     if (g.fused) {
         // k updates take k + 1 launches, an even number per chunk
         want += 1;
@@ -2146,6 +2170,8 @@ ppcg_status Engine::add(ppcg_handle *h, int mixed, double tol, const double *, i
     j.mixed = mixed;
     j.tol = tol;
     j.x0_zero = h->x0_zero;
+    const ByteModel bm = byte_model(h, mixed == MIX_INNER32 ? PREC_F32 : mixed == MIX_VALUES32 ? PREC_V32 : PREC_F64);
+    j.iter_bytes = bm.vma + bm.spmv;
     j.t_start = now_ms();
     const ppcg_options &o = h->opt;
     const int stop = o.stop == PPCG_STOP_PRECOND_ABS ? STOP_ABS : STOP_REL;
@@ -2597,7 +2623,8 @@ ppcg_status Engine::step(int graph_iters)
                 j.stage = JS_NEED_FINAL;
             }
         } else {
-            note_progress(d, st, &j.last_norm, &j.last_iter, &j.rate);
+            note_progress(d, st, &j.last_norm, &j.last_iter, &j.rate,
+                          j.x0_zero && j.restarts == 0 && j.mixed == MIX_NONE);
         }
     }
     return PPCG_OK;
