@@ -124,6 +124,7 @@ struct ppcg_handle {
     double *sval = nullptr;
     unsigned long long *smask = nullptr;
     int smaxlen = 0;
+    int srun = 0;  // some chunk's list is runs of consecutive columns
     ppcg::DevArena st_arena;
     int *perm = nullptr, *invperm = nullptr;
     double *val64 = nullptr;  // FP64 values in the stored format
@@ -216,12 +217,16 @@ enum JobStage {
     JS_DONE = 5
 };
 
+// Kernel of a single-launch group: k_fused, k_stencil, k_stencil with runs.
+enum StencilKernel { ST_NONE = 0, ST_LISTS, ST_RUNS };
+
 // Per-precision set of system slots, work table and captured graph.
 struct Group {
     int prec = PREC_F64;
     bool pcg = false;               // iterates Algorithm 1, two launches per iteration (work items are fused tiles)
     bool fused = false;             // FP64 PIPECG, one launch per iteration (work items are fused tiles)
     bool stencil = false;           // ... of k_stencil instead of k_fused
+    StencilKernel g_stencil = ST_NONE;  // its form in the captured graphs
     int cap_sys = 0;
     SysDesc *desc_d = nullptr;
     SysState *st_d = nullptr;
@@ -405,10 +410,10 @@ void launch_pipecg_iter(hipStream_t s, const WorkItem *tab, const int *cnt, cons
 void launch_pipecg_init_fused(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid,
                               bool x_zero = false);
 // K launches of the single-launch form over a table of fused tiles (K even),
-// preceded by k_fused_begin; stencil: k_stencil instead of k_fused; solo: the
+// preceded by k_fused_begin; stencil: the kernel; solo: the
 // only system's descriptor, when the table holds its tiles in order (or NULL).
 void launch_fused_chunk(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int iters,
-                        bool stencil, const SysDesc *solo);
+                        StencilKernel stencil, const SysDesc *solo);
 // Allocate the single-launch form's buffers of a handle (once).
 ppcg_status ensure_fused(ppcg_handle *h);
 // Fused tiles of a handle's system (fused_tile_rows(n, cus) rows each).

@@ -259,6 +259,7 @@ struct SysDesc {
     double *shist;        // 2 slots (launch parity) of alpha[kStDefer], beta[kStDefer]
     int vstride;          // bytes between two of the FP64 vectors x r u w m nv z q s p
     int smaxlen;          // entries of the longest list
+    int srun;             // some chunk's list is runs of consecutive columns (ppcg_lists.hpp)
     int sring;            // 1: k_stencil keeps kStDefer residuals and updates p and x together
     const void *val;      // matrix values (double or float)
     const float *val32;   // FP32 copy of the values (vals32 mode)

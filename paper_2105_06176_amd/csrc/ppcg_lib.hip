@@ -491,6 +491,7 @@ ppcg_status fill_desc(ppcg_handle *h, int prec, SysState *st, SysDesc *d, double
         d->sval = h->sval;
         d->smask = h->smask;
         d->smaxlen = h->smaxlen;
+        d->srun = h->srun;
         d->shist = h->shist;
         d->vstride = (int)((char *)pd.vec[VR] - (char *)pd.vec[VX]);
         d->sring = stencil_ring(h->n) ? 1 : 0;
@@ -1157,10 +1158,12 @@ static ppcg_status build_stencil(ppcg_handle *h)
     const hipError_t es = hipStreamSynchronize(s);
     if (e == hipSuccess)
         e = es;
-    if (e != hipSuccess || bad)  // bad: two different lists of one hash
+    if (e != hipSuccess || (bad & 1u)) {  // two different lists of one hash
         drop_stencil(h);
-    else
+    } else {
         h->schunk = schunk;
+        h->srun = bad >> 1;
+    }
     h->smaxlen = longest;
     PPCG_HIP(e);
     return PPCG_OK;
@@ -1775,20 +1778,26 @@ void launch_pipecg_init_fused(hipStream_t s, const WorkItem *tab, const int *cnt
     k_spmv<double, MODE_INIT2><<<grid, kSpmvThreads, 0, s>>>(tab, cnt, dd, rs);
 }
 
+static decltype(&k_stencil<true, true>) stencil_kernel(StencilKernel k, bool solo)
+{
+    if (k == ST_RUNS)
+        return solo ? k_stencil<true, true> : k_stencil<false, true>;
+    return solo ? k_stencil<true, false> : k_stencil<false, false>;
+}
+
 // One launch of the single-launch form with parity i & 1.
 static void launch_fused(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int i,
-                         bool stencil, const SysDesc *solo)
+                         StencilKernel stencil, const SysDesc *solo)
 {
-    if (stencil && solo)
-        k_stencil<true><<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1, *solo);
-    else if (stencil)
-        k_stencil<false><<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1, SysDesc{});
+    if (stencil != ST_NONE)
+        stencil_kernel(stencil, solo != nullptr)<<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1,
+                                                                                solo ? *solo : SysDesc{});
     else
         k_fused<<<grid, kFusedThreads, 0, s>>>(tab, cnt, dd, PPCG_FUSED_REMAP, i & 1);
 }
 
 void launch_fused_chunk(hipStream_t s, const WorkItem *tab, const int *cnt, const SysDesc *dd, int grid, int iters,
-                        bool stencil, const SysDesc *solo)
+                        StencilKernel stencil, const SysDesc *solo)
 {
     k_fused_begin<<<grid, 64, 0, s>>>(tab, cnt, dd);
     for (int i = 0; i < iters; ++i)
@@ -1910,6 +1919,15 @@ ppcg_status Engine::ensure_graph(Group &g, int iters, hipGraphExec_t *exec)
     if (g.g_grid < need || g.g_grid > std::max(need * 4, 64) ||
         (g.pcg && (g.g_sys_grid < need_sys || g.g_sys_grid > std::max(need_sys * 4, 16))))
         drop_graphs(g);
+    // k_stencil's form: by the systems that iterate now
+    StencilKernel stencil = g.stencil ? ST_LISTS : ST_NONE;
+    if (g.stencil)
+        for (const WorkItem &w : g.table_h)
+            if (w.tile == 0 && g.desc_h[w.slot].srun)
+                stencil = ST_RUNS;
+    if (stencil != g.g_stencil)
+        drop_graphs(g);
+    g.g_stencil = stencil;
     // an engine of one system: its graphs hold the descriptor, without the
     // options
     const bool solo = g.stencil && g.cap_sys == 1;
@@ -1933,7 +1951,7 @@ ppcg_status Engine::ensure_graph(Group &g, int iters, hipGraphExec_t *exec)
     Group::CapturedGraph cg;
     PPCG_HIP(hipStreamBeginCapture(stream_, hipStreamCaptureModeThreadLocal));
     if (g.fused)
-        launch_fused_chunk(stream_, g.table_d, g.count_d, g.desc_d, grid, iters, g.stencil,
+        launch_fused_chunk(stream_, g.table_d, g.count_d, g.desc_d, grid, iters, stencil,
                            solo ? &g.solo : nullptr);
     else
         launch_iters(stream_, g, grid, remap, iters);
@@ -3298,15 +3316,15 @@ ppcg_status ppcg_time_kernels(ppcg_handle *h, const double *b, int32_t iters, do
         const int fgrid = fused_tiles(h);
         launch_pipecg_init_fused(s, tab, cnt, dd, grid);
         k_fused_begin<<<fgrid, 64, 0, s>>>(tab, cnt + 1, dd);
-        const bool stencil = h->schunk != nullptr;
+        const StencilKernel stencil = !h->schunk ? ST_NONE : h->srun ? ST_RUNS : ST_LISTS;
         SysDesc own;
         PPCG_TRY(fill_desc(h, PREC_F64, h->plain_st, &own, 0.0, INT_MAX, INT_MAX, STOP_REL));
         launch_fused(s, tab, cnt + 1, dd, fgrid, 0, stencil, &own);
         for (auto &e : ev)
             PPCG_HIP_CLEAN(hipEventCreate(&e), clean());
         for (int i = 1; i <= iters; ++i) {
-            if (stencil)
-                hipExtLaunchKernelGGL(k_stencil<true>, dim3(fgrid), dim3(kFusedThreads), 0, s, ev[4 * (i - 1)],
+            if (stencil != ST_NONE)
+                hipExtLaunchKernelGGL(stencil_kernel(stencil, true), dim3(fgrid), dim3(kFusedThreads), 0, s, ev[4 * (i - 1)],
                                       ev[4 * (i - 1) + 1], 0, tab, cnt + 1, dd, (int)PPCG_FUSED_REMAP, i & 1, own);
             else
                 hipExtLaunchKernelGGL(k_fused, dim3(fgrid), dim3(kFusedThreads), 0, s, ev[4 * (i - 1)],

@@ -25,8 +25,8 @@
 // the chunk lists, then also with the ring of residuals (kStDefer): 128^3
 // 7-point 49.4, 32.0, 29.5 (164 MB in the last: 5.6 TB/s, of which about
 // 5 us are the launch's start and its reduction); 100^3 26.7, 18.6, 17.4;
-// 165^3 125-point 471, 278, 278 (no ring at that size); 301^2 5-point 6.6,
-// 5.8, 5.8.  Streaming hints (nt) on the loads or stores: 36 to 44 us at
+// 165^3 125-point 471, 278, 278 (no ring at that size), 150 with st_row_runs
+// (100^3 27-point 20.3 and 16.9); 301^2 5-point 6.6, 5.8, 5.8.  Streaming hints (nt) on the loads or stores: 36 to 44 us at
 // 128^3, because the vectors then miss the memory-side cache.  Forming z from
 // s in every launch (z = A M^-1 s, gathered beside w, instead of z carried;
 // 16 bytes per row fewer) measured no faster at 7 points and twice slower at
@@ -108,12 +108,13 @@ __global__ __launch_bounds__(64) void k_st_copy(const int4 *__restrict__ items, 
     }
 }
 
-// flag[0] |= 1 when a chunk's lists differ from the ones it was given.
+// flag[0] |= 1 when a chunk's lists differ from the ones it was given, 2 when
+// st_row_runs has a step to do on it.
 __global__ __launch_bounds__(64) void k_st_verify(int nchunks, const int64_t *__restrict__ cptr,
                                                   const int *__restrict__ cpat, const int *__restrict__ pats,
                                                   const double *__restrict__ tval,
                                                   const unsigned long long *__restrict__ tmask,
-                                                  const int4 *__restrict__ chunk, const int *__restrict__ off,
+                                                  int4 *__restrict__ chunk, const int *__restrict__ off,
                                                   const double *__restrict__ val,
                                                   const unsigned long long *__restrict__ mask,
                                                   unsigned *__restrict__ flag)
@@ -132,6 +133,19 @@ __global__ __launch_bounds__(64) void k_st_verify(int nchunks, const int64_t *__
               mask[ch.y + k] != tmask[base / kSellC + k];
     if (bad)
         atomicOr(flag, 1u);
+    // the length of the runs that the whole list consists of
+    bool run5 = len > 0 && len % 5 == 0, run3 = len > 0 && len % 3 == 0;
+    for (int k = threadIdx.x; k < len; k += 64) {
+        const bool next = k > 0 && list[k] == list[k - 1] + 1;
+        run5 = run5 && (k % 5 == 0 || next);
+        run3 = run3 && (k % 3 == 0 || next);
+    }
+    const int run = __all(run5) ? 5 : __all(run3) ? 3 : 0;
+    if (threadIdx.x == 0) {
+        chunk[c].w = run;
+        if (run && len >= kStRuns * run)
+            atomicOr(flag, 2u);
+    }
 }
 
 // ---------------------------------------------------------------- iteration
@@ -153,6 +167,18 @@ __device__ __forceinline__ void st_put(StBuf v, int byte, int vec, double x)
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(uvec2, x), v, byte, vec, 0);
 }
 
+template <bool RUNS>
+__device__ __forceinline__ double st_row_any(const SysDesc &d, StChunk ch, StBuf w, int rowb, double d0, double *wl)
+{
+    if constexpr (RUNS) {
+        if (ch[3] == 5)
+            return st_row_runs<5>(d, ch, w, rowb, d0, wl);
+        if (ch[3] == 3)
+            return st_row_runs<3>(d, ch, w, rowb, d0, wl);
+    }
+    return st_row<true>(d, ch, w, rowb, d0);
+}
+
 // k_fused (see ppcg_fused.hpp for the steps) with rows read from the lists;
 // the diagonal is constant.  The registers stay at 61 (8 wavefronts per
 // SIMD): local copies that the compiler cannot split went to LDS, with
@@ -162,7 +188,9 @@ __device__ __forceinline__ void st_put(StBuf v, int byte, int vec, double x)
 // with the kernel's arguments (the options in it do not: they are read from
 // descs[0], so that a captured launch stays valid when they change).  It saves
 // two dependent loads at the start of every launch.
-template <bool SOLO>
+// RUNS: some system of the launch has lists of runs (a kernel of its own: with
+// both in one, 7-point rows at 128^3 lost 2 % to the extra registers).
+template <bool SOLO, bool RUNS>
 __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(const WorkItem *__restrict__ table,
                                                                              const int *__restrict__ count,
                                                                              const SysDesc *__restrict__ descs,
@@ -170,6 +198,7 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
 {
     __shared__ double lds[kFusedThreads / 64 * kNumPartials];
     __shared__ StScalars sc;
+    __shared__ double win[RUNS ? kFusedThreads / 64 * kStRunLds : 1];
     const int live = SOLO ? own.nftiles : *count;
     if ((int)blockIdx.x >= live)
         return;
@@ -234,7 +263,7 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
     double w = st_load(wb, ib), s = st_vec(V, ib, oS), z = st_vec(V, ib, oZ), r = st_vec(V, ib, oR);
     double nv = 0.0;
     if (some)
-        nv = st_row<true>(d, ch, wb, (row0 + tid) * 8, d0);
+        nv = st_row_any<RUNS>(d, ch, wb, (row0 + tid) * 8, d0, win + (RUNS ? wave * kStRunLds : 0));
     // 1. The previous launch's partials and the scalar recurrences.
     {
         double v[kNumPartials] = {0.0, 0.0, 0.0, 0.0};
@@ -308,7 +337,7 @@ __global__ __launch_bounds__(kFusedThreads, PPCG_FUSED_WAVES) void k_stencil(con
             z = st_vec(V, ib, oZ);
             r = st_vec(V, ib, oR);
             ch = CH[c0 + k * (kFusedThreads / kSellC)];
-            nv = st_row<true>(d, ch, wb, i * 8, d0);
+            nv = st_row_any<RUNS>(d, ch, wb, i * 8, d0, win + (RUNS ? wave * kStRunLds : 0));
         }
         if (ring) {
             if (full) {

@@ -104,6 +104,49 @@ def test_lists_equal_columns_and_oracle(name):
         s.close()
 
 
+def runs(nx, ny, nz, rx, ry, rz):
+    """Runs of 2 rx + 1 consecutive columns, (2 ry + 1) (2 rz + 1) of them."""
+    offs = [(i, j, k) for k in range(-rz, rz + 1) for j in range(-ry, ry + 1) for i in range(-rx, rx + 1)]
+    return _constant_stencil((nx, ny, nz), offs, len(offs) - 0.5, -1.0, f"runs_{nx}_{ny}_{nz}_{rx}{ry}{rz}")
+
+
+# steps of three runs, what remains after them, runs on the edges of the vector and of its lines
+RUNS = [(1000, 1, 1, 2, 0, 0), (100, 60, 1, 2, 1, 0), (61, 97, 1, 2, 2, 0), (90, 70, 1, 1, 1, 0), (40, 40, 40, 1, 1, 1),
+        (64, 60, 30, 1, 1, 1), (53, 50, 41, 2, 2, 2), (65, 40, 40, 2, 1, 2), (101, 50, 1, 3, 1, 0)]
+# rows sorted by length: per-entry columns
+SORTED = [(33, 20, 17, 1, 1, 1), (3, 40, 40, 1, 1, 1), (5, 30, 31, 2, 2, 2), (37, 11, 13, 2, 2, 2)]
+
+
+@pytest.mark.parametrize("shape", RUNS + SORTED, ids=lambda t: "_".join(map(str, t)))
+def test_runs_equal_columns_and_oracle(shape):
+    A = runs(*shape)
+    b = rhs_from_solution(A, xstar_uniform(A.n, 4))
+    S = Solver(A, fixed_iters=8, spmv_format="sell", flags=LISTS)
+    N = Solver(A, fixed_iters=8, spmv_format="sell", flags=COLUMNS)
+    assert (S.matrix_info()["col_index_bytes"] == 0) == (shape in RUNS)
+    x, info = S.solve(dev(b))
+    y, _ = N.solve(dev(b))
+    ref = oracle.pipecg(A, b, fixed_iters=8)
+    assert info["status"] == ppcg.OK and info["iters"] == ref.iters
+    assert np.array_equal(host(x), host(y))
+    assert np.linalg.norm(host(x) - ref.x) <= 1e-10 * np.linalg.norm(ref.x)
+    S.close()
+    N.close()
+
+
+def test_batch_with_and_without_runs_equals_solo_bitwise():
+    mats = [poisson3d(20), runs(53, 50, 41, 2, 2, 2), poisson2d(80), runs(40, 40, 40, 1, 1, 1)]
+    bs = [rhs_from_solution(A, xstar_uniform(A.n, 5 + i)) for i, A in enumerate(mats)]
+    solvers = [Solver(A, tol=1e-9, spmv_format="sell", flags=LISTS) for A in mats]
+    solo = [s.solve(dev(b)) for s, b in zip(solvers, bs)]
+    for _ in range(2):
+        xs, infos = solve_batch(solvers, [dev(b) for b in bs])
+        for x, info, (y, one) in zip(xs, infos, solo):
+            assert info["iters"] == one["iters"] and np.array_equal(host(x), host(y))
+    for s in solvers:
+        s.close()
+
+
 @pytest.mark.parametrize("name", ["poisson2d_67", "lines_of_63", "poisson125_40", "halves_inside_a_chunk"])
 def test_spmv_and_initial_guess_on_lists(name):
     """The SpMV, the initialisation from a guess and the true residual read the lists too (no value table is built):
