@@ -1075,7 +1075,7 @@ static void shared_for_fused(ppcg_handle *h)
 static ppcg_status build_stencil(ppcg_handle *h)
 {
     const unsigned fl = h->opt.flags;
-    if (h->fmt != FMT_SELL || !h->cpat || h->perm || !h->dinv_const || h->n > kStMaxRows ||
+    if (h->schunk || h->fmt != FMT_SELL || !h->cpat || h->perm || !h->dinv_const || h->n > kStMaxRows ||
         (fl & (PPCG_FLAG_SELL_COL16 | PPCG_FLAG_SELL_COL32 | PPCG_FLAG_SELL_NO_SHARED_OFFSETS |
                PPCG_FLAG_SELL_FULL_VALUES | PPCG_FLAG_ITER_TWO_LAUNCH)) != 0)
         return PPCG_OK;
@@ -1387,6 +1387,30 @@ static ppcg_status choose_format(ppcg_handle *h, const int *rp, const int *ci, c
         PPCG_TRY(adopt_csrv(h, csrv_default_lanes(mean), rp, ci, val));
         return bind_f64(h, dinv_orig);
     }
+    // A matrix whose unsorted SELL chunks have lists (a constant-coefficient
+    // stencil) takes them untimed: its iterations read no storage per entry,
+    // and the candidates' SpMV timings, on per-entry columns, say nothing about
+    // them.  Per solve, with the timed choice where it fell elsewhere and with
+    // the lists: 16^3 125-point 1150, 630 us; 19 x 160 x 90 1510, 910 us.
+    // Up to kListPadding stored entries per entry: rows much shorter than their
+    // chunk's list go on to the timing.
+    constexpr double kListPadding = 1.5;
+    bool unsorted = false;  // the unsorted SELL layout is in place
+    if (shared && !forced16 && h->dinv_const && h->opt.precision == PPCG_FP64) {
+        int64_t st1 = 0;
+        PPCG_TRY(sell_size(h->stream, h->n, 1, rowlen, &st1));
+        if ((double)st1 <= kListPadding * (double)h->nnz) {
+            SellBuild sb;
+            PPCG_TRY(build_sell(h->stream, h->n, 1, rp, ci, val, rowlen, &sb, shared));
+            PPCG_TRY(adopt_sell(h, sb));
+            PPCG_TRY(bind_f64(h, dinv_orig));
+            PPCG_TRY(build_stencil(h));
+            if (h->schunk)
+                return PPCG_OK;
+            drop_stencil(h);
+            unsorted = true;
+        }
+    }
     TuneKey key{(int)std::log2((double)h->n), (int)std::lround(mean), (int)std::lround(10 * cv),
                 (int)std::log2((double)std::max(mx, 1))};
     TuneVal tv{};
@@ -1403,7 +1427,8 @@ static ppcg_status choose_format(ppcg_handle *h, const int *rp, const int *ci, c
         }
     }
     if (hit) {
-        if (tv.fmt == FMT_SELL) {
+        if (tv.fmt == FMT_SELL && tv.sigma == 1 && unsorted) {  // in place
+        } else if (tv.fmt == FMT_SELL) {
             SellBuild sb;
             PPCG_TRY(build_sell(h->stream, h->n, tv.sigma, rp, ci, val, rowlen, &sb, shared));
             PPCG_TRY(adopt_sell(h, sb));
@@ -1456,7 +1481,8 @@ static ppcg_status choose_format(ppcg_handle *h, const int *rp, const int *ci, c
     double best = 1e300;
     Cand bestc = cands[0];
     for (const Cand &c : cands) {
-        if (c.fmt == FMT_SELL) {
+        if (&c == &cands[0] && unsorted) {  // in place
+        } else if (c.fmt == FMT_SELL) {
             SellBuild sb;
             PPCG_TRY(build_sell(h->stream, h->n, c.sigma, rp, ci, val, rowlen, &sb, shared));
             PPCG_TRY(adopt_sell(h, sb));

@@ -134,6 +134,37 @@ def test_runs_equal_columns_and_oracle(shape):
     N.close()
 
 
+# matrix, whether the lists are taken untimed (else left to the timing)
+AUTO = {
+    "runs_16_16_16": (lambda: runs(16, 16, 16, 2, 2, 2), True),
+    "runs_17_30_23": (lambda: runs(17, 30, 23, 2, 2, 2), True),
+    "runs_33_20_17": (lambda: runs(33, 20, 17, 1, 1, 1), True),
+    "runs_5_30_31": (lambda: runs(5, 30, 31, 2, 2, 2), False),  # 2.1 stored entries per entry
+    "poisson2d_33": (lambda: poisson2d(33), True),
+    "box_24_40_18": (lambda: box(24, 40, 18), True),
+    "halves": (lambda: halves(6400, 3220), False),  # two values of an entry in a chunk
+    "one_row": (CASES["one_row"][0], True),
+}
+
+
+@pytest.mark.parametrize("name", sorted(AUTO))
+@pytest.mark.parametrize("k", [1, 9])
+def test_automatic_choice_and_oracle(name, k):
+    gen, lists = AUTO[name]
+    A = gen()
+    k = min(k, A.n)
+    b = rhs_from_solution(A, xstar_uniform(A.n, 6))
+    ref = oracle.pipecg(A, b, fixed_iters=k)
+    for _ in range(2):  # the second handle meets what the first one left
+        S = Solver(A, fixed_iters=k)
+        if lists:
+            assert S.matrix_info()["col_index_bytes"] == 0
+        x, info = S.solve(dev(b))
+        assert info["status"] == ppcg.OK and info["iters"] == ref.iters
+        assert np.linalg.norm(host(x) - ref.x) <= 1e-10 * np.linalg.norm(ref.x)
+        S.close()
+
+
 def test_batch_with_and_without_runs_equals_solo_bitwise():
     mats = [poisson3d(20), runs(53, 50, 41, 2, 2, 2), poisson2d(80), runs(40, 40, 40, 1, 1, 1)]
     bs = [rhs_from_solution(A, xstar_uniform(A.n, 5 + i)) for i, A in enumerate(mats)]
