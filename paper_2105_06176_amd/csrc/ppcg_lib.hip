@@ -66,13 +66,139 @@ double now_ms()
 
 static inline unsigned blocks_for(size_t n, unsigned bs) { return (unsigned)((n + bs - 1) / bs); }
 
+// ---------------------------------------------------------------- pool
+DevPool::Use &DevPool::use()
+{
+    static thread_local Use u;
+    return u;
+}
+
+std::mutex &DevPool::reg_mu()
+{
+    static std::mutex m;
+    return m;
+}
+
+std::unordered_map<void *, std::pair<DevPool *, size_t>> &DevPool::reg()
+{
+    static std::unordered_map<void *, std::pair<DevPool *, size_t>> r;
+    return r;
+}
+
+DevPool::~DevPool()
+{
+    trim(0);
+    for (hipStream_t s : streams_)
+        (void)hipStreamDestroy(s);
+    std::lock_guard<std::mutex> lk(reg_mu());
+    for (auto it = reg().begin(); it != reg().end();)  // (blocks still out are released by hipFree)
+        it = it->second.first == this ? reg().erase(it) : std::next(it);
+}
+
+hipError_t DevPool::take(void **p, size_t bytes)
+{
+    size_t size = 512;  // powers of two and the three sizes between them
+    while (size < bytes)
+        size *= 2;
+    if (size > 2048)
+        for (int q = 5; q < 8; ++q)
+            if (size / 8 * q >= bytes) {
+                size = size / 8 * q;
+                break;
+            }
+    if (size > kMaxBlock)
+        return hipMalloc(p, bytes);
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        auto it = idle_.find(size);
+        if (it != idle_.end()) {
+            *p = it->second;
+            idle_.erase(it);
+            idle_bytes_ -= size;
+            return hipSuccess;
+        }
+    }
+    hipError_t e = hipMalloc(p, size);
+    if (e == hipErrorOutOfMemory) {
+        trim(0);
+        (void)hipGetLastError();
+        e = hipMalloc(p, size);
+    }
+    if (e != hipSuccess)
+        return e;
+    std::lock_guard<std::mutex> lk(reg_mu());
+    reg()[*p] = {this, size};
+    return hipSuccess;
+}
+
+bool DevPool::give(void *p)
+{
+    std::pair<DevPool *, size_t> b;
+    {
+        std::lock_guard<std::mutex> lk(reg_mu());
+        auto it = reg().find(p);
+        if (it == reg().end())
+            return false;
+        b = it->second;
+    }
+    if (use().stream)
+        (void)hipStreamSynchronize(use().stream);
+    std::unique_lock<std::mutex> lk(b.first->mu_);
+    b.first->idle_.emplace(b.second, p);
+    b.first->idle_bytes_ += b.second;
+    lk.unlock();
+    b.first->trim(kMaxIdle);
+    return true;
+}
+
+void DevPool::trim(size_t keep)
+{
+    std::vector<void *> drop;
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        while (idle_bytes_ > keep) {  // the largest first
+            auto it = std::prev(idle_.end());
+            drop.push_back(it->second);
+            idle_bytes_ -= it->first;
+            idle_.erase(it);
+        }
+    }
+    for (void *p : drop) {
+        {
+            std::lock_guard<std::mutex> lk(reg_mu());
+            reg().erase(p);
+        }
+        std::shared_lock<std::shared_mutex> lk(release_mu());
+        (void)hipFree(p);
+    }
+}
+
+hipStream_t DevPool::take_stream()
+{
+    std::lock_guard<std::mutex> lk(mu_);
+    if (streams_.empty())
+        return nullptr;
+    hipStream_t s = streams_.back();
+    streams_.pop_back();
+    return s;
+}
+
+bool DevPool::give_stream(hipStream_t s)
+{
+    std::lock_guard<std::mutex> lk(mu_);
+    if (streams_.size() >= kMaxStreams)
+        return false;
+    streams_.push_back(s);
+    return true;
+}
+
 // ---------------------------------------------------------------- arena
 ppcg_status DevArena::alloc(size_t bytes)
 {
     release();
     if (bytes == 0)
         bytes = 256;
-    hipError_t e = hipMalloc((void **)&base, bytes);
+    hipError_t e = dev_alloc(&base, bytes);
     if (e != hipSuccess) {
         base = nullptr;
         set_error("hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
@@ -233,10 +359,10 @@ static ppcg_status sell_size(hipStream_t s, int n, int sigma, const int *rowlen,
         if (sz) (void)dev_free(sz);
         if (cp) (void)dev_free(cp);
     };
-    PPCG_HIP_CLEAN(hipMalloc(&sz, sizeof(int64_t) * nchunks), clean());
-    PPCG_HIP_CLEAN(hipMalloc(&cp, sizeof(int64_t) * (nchunks + 1)), clean());
+    PPCG_HIP_CLEAN(dev_alloc(&sz, sizeof(int64_t) * nchunks), clean());
+    PPCG_HIP_CLEAN(dev_alloc(&cp, sizeof(int64_t) * (nchunks + 1)), clean());
     if (sigma > 1) {
-        PPCG_HIP_CLEAN(hipMalloc(&perm, sizeof(int) * n), clean());
+        PPCG_HIP_CLEAN(dev_alloc(&perm, sizeof(int) * n), clean());
         launch_sort_window(s, n, sigma, rowlen, perm);
     }
     k_chunk_size<<<blocks_for(nchunks, 256), 256, 0, s>>>(n, nchunks, perm, rowlen, sz);
@@ -258,7 +384,7 @@ static ppcg_status widen_for_shared(hipStream_t s, int n, int nchunks, const int
 {
     *ok = false;
     int *cnt = nullptr;
-    PPCG_HIP(hipMalloc(&cnt, sizeof(int) * std::max(nchunks, 1)));
+    PPCG_HIP(dev_alloc(&cnt, sizeof(int) * std::max(nchunks, 1)));
     std::vector<int> cnt_h((size_t)nchunks);
     std::vector<int64_t> sz_h((size_t)nchunks);
     k_sell_union_count<<<nchunks, kSellC, 0, s>>>(n, nchunks, rp, ci, sz, cnt);
@@ -307,8 +433,8 @@ static ppcg_status build_shared_lists(hipStream_t s, int n, const int *rp, const
         return PPCG_OK;
     const unsigned zero = 0u;
     unsigned bad = 1u;
-    PPCG_HIP_CLEAN(hipMalloc(&lists, sizeof(int) * nl), clean());
-    PPCG_HIP_CLEAN(hipMalloc(&flag, sizeof(unsigned)), clean());
+    PPCG_HIP_CLEAN(dev_alloc(&lists, sizeof(int) * nl), clean());
+    PPCG_HIP_CLEAN(dev_alloc(&flag, sizeof(unsigned)), clean());
     PPCG_HIP_CLEAN(hipMemcpyAsync(flag, &zero, sizeof zero, hipMemcpyHostToDevice, s), clean());
     k_sell_union<<<sb.nchunks, kSellC, 0, s>>>(n, sb.nchunks, rp, ci, sb.cptr, lists, flag);
     PPCG_HIP_CLEAN(hipGetLastError(), clean());
@@ -343,8 +469,8 @@ static ppcg_status build_shared_lists(hipStream_t s, int n, const int *rp, const
     }
     if (pats.empty())
         pats.push_back(0);
-    PPCG_HIP(hipMalloc(&sb.cpat, sizeof(int) * cpat.size()));
-    PPCG_HIP(hipMalloc(&sb.pats, sizeof(int) * pats.size()));
+    PPCG_HIP(dev_alloc(&sb.cpat, sizeof(int) * cpat.size()));
+    PPCG_HIP(dev_alloc(&sb.pats, sizeof(int) * pats.size()));
     PPCG_HIP(hipMemcpyAsync(sb.cpat, cpat.data(), sizeof(int) * cpat.size(), hipMemcpyHostToDevice, s));
     PPCG_HIP(hipMemcpyAsync(sb.pats, pats.data(), sizeof(int) * pats.size(), hipMemcpyHostToDevice, s));
     PPCG_HIP(hipStreamSynchronize(s));
@@ -367,11 +493,11 @@ static ppcg_status build_sell(hipStream_t s, int n, int sigma, const int *rp, co
         if (sz) (void)dev_free(sz);
         sb.free_all();
     };
-    PPCG_HIP_CLEAN(hipMalloc(&sz, sizeof(int64_t) * sb.nchunks), clean());
-    PPCG_HIP_CLEAN(hipMalloc(&sb.cptr, sizeof(int64_t) * (sb.nchunks + 1)), clean());
+    PPCG_HIP_CLEAN(dev_alloc(&sz, sizeof(int64_t) * sb.nchunks), clean());
+    PPCG_HIP_CLEAN(dev_alloc(&sb.cptr, sizeof(int64_t) * (sb.nchunks + 1)), clean());
     if (sigma > 1) {
-        PPCG_HIP_CLEAN(hipMalloc(&sb.perm, sizeof(int) * n), clean());
-        PPCG_HIP_CLEAN(hipMalloc(&sb.invperm, sizeof(int) * n), clean());
+        PPCG_HIP_CLEAN(dev_alloc(&sb.perm, sizeof(int) * n), clean());
+        PPCG_HIP_CLEAN(dev_alloc(&sb.invperm, sizeof(int) * n), clean());
         launch_sort_window(s, n, sigma, rowlen, sb.perm);
         k_invert_perm<<<blocks_for(n, 256), 256, 0, s>>>(n, sb.perm, sb.invperm);
     }
@@ -388,8 +514,8 @@ static ppcg_status build_sell(hipStream_t s, int n, int sigma, const int *rp, co
     PPCG_HIP_CLEAN(hipMemcpyAsync(&sb.stored, sb.cptr + sb.nchunks, sizeof(int64_t), hipMemcpyDeviceToHost, s),
                    clean());
     PPCG_HIP_CLEAN(hipStreamSynchronize(s), clean());
-    PPCG_HIP_CLEAN(hipMalloc(&sb.col, sizeof(int) * std::max<int64_t>(sb.stored, 1)), clean());
-    PPCG_HIP_CLEAN(hipMalloc(&sb.val, sizeof(double) * std::max<int64_t>(sb.stored, 1)), clean());
+    PPCG_HIP_CLEAN(dev_alloc(&sb.col, sizeof(int) * std::max<int64_t>(sb.stored, 1)), clean());
+    PPCG_HIP_CLEAN(dev_alloc(&sb.val, sizeof(double) * std::max<int64_t>(sb.stored, 1)), clean());
     if (widened) {
         const ppcg_status rc = build_shared_lists(s, n, rp, ci, sb);
         if (rc < 0) {
@@ -401,7 +527,7 @@ static ppcg_status build_sell(hipStream_t s, int n, int sigma, const int *rp, co
         unsigned *flag = nullptr;
         const unsigned zero = 0u;
         unsigned bad = 1u;
-        hipError_t e = hipMalloc(&flag, sizeof(unsigned));
+        hipError_t e = dev_alloc(&flag, sizeof(unsigned));
         if (e == hipSuccess)
             e = hipMemcpyAsync(flag, &zero, sizeof zero, hipMemcpyHostToDevice, s);
         if (e == hipSuccess) {
@@ -566,10 +692,10 @@ static ppcg_status plain_setup(ppcg_handle *h, double tol, int fixed, int maxit)
 {
     hipStream_t s = h->stream;
     if (!h->plain_desc) {
-        PPCG_HIP(hipMalloc(&h->plain_desc, sizeof(SysDesc)));
-        PPCG_HIP(hipMalloc(&h->plain_st, sizeof(SysState)));
-        PPCG_HIP(hipMalloc(&h->plain_tab, sizeof(WorkItem) * h->ntiles));
-        PPCG_HIP(hipMalloc(&h->plain_cnt, sizeof(int) * 3));  // [1]: fused tiles, [2]: classic PCG's
+        PPCG_HIP(dev_alloc(&h->plain_desc, sizeof(SysDesc)));
+        PPCG_HIP(dev_alloc(&h->plain_st, sizeof(SysState)));
+        PPCG_HIP(dev_alloc(&h->plain_tab, sizeof(WorkItem) * h->ntiles));
+        PPCG_HIP(dev_alloc(&h->plain_cnt, sizeof(int) * 3));  // [1]: fused tiles, [2]: classic PCG's
         std::vector<WorkItem> th(h->ntiles);
         for (int t = 0; t < h->ntiles; ++t)
             th[t] = {0, t};
@@ -693,8 +819,8 @@ static ppcg_status build_col16(ppcg_handle *h, bool *built)
     unsigned nofit = 1u;
     const unsigned zero = 0u;
     hipStream_t s = h->stream;
-    PPCG_HIP(hipMalloc(&c16, sizeof(short) * std::max<int64_t>(h->nnz_stored, 1)));
-    hipError_t e = hipMalloc(&flag, sizeof(unsigned));
+    PPCG_HIP(dev_alloc(&c16, sizeof(short) * std::max<int64_t>(h->nnz_stored, 1)));
+    hipError_t e = dev_alloc(&flag, sizeof(unsigned));
     if (e == hipSuccess)
         e = hipMemcpyAsync(flag, &zero, sizeof zero, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
@@ -884,11 +1010,11 @@ static ppcg_status build_vtab(ppcg_handle *h, const std::vector<uint64_t> &keys)
     double *tab = nullptr;
     unsigned *flag = nullptr;
     unsigned zero = 0u, bad = 0u;
-    hipError_t e = hipMalloc(&vi, (size_t)std::max<int64_t>(h->nnz_stored, 1));
+    hipError_t e = dev_alloc(&vi, (size_t)std::max<int64_t>(h->nnz_stored, 1));
     if (e == hipSuccess)
-        e = hipMalloc(&tab, sizeof(double) * nt);
+        e = dev_alloc(&tab, sizeof(double) * nt);
     if (e == hipSuccess)
-        e = hipMalloc(&flag, sizeof(unsigned));
+        e = dev_alloc(&flag, sizeof(unsigned));
     if (e == hipSuccess)
         e = hipMemcpyAsync(tab, keys.data(), sizeof(double) * nt, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
@@ -1315,9 +1441,9 @@ static ppcg_status adopt_csrv(ppcg_handle *h, int lanes, const int *rp, const in
     h->lanes = lanes;
     h->nchunks = 0;
     h->nnz_stored = h->nnz;
-    PPCG_HIP(hipMalloc(&h->rp, sizeof(int) * (h->n + 1)));
-    PPCG_HIP(hipMalloc(&h->col, sizeof(int) * std::max<int64_t>(h->nnz, 1)));
-    PPCG_HIP(hipMalloc(&h->val64, sizeof(double) * std::max<int64_t>(h->nnz, 1)));
+    PPCG_HIP(dev_alloc(&h->rp, sizeof(int) * (h->n + 1)));
+    PPCG_HIP(dev_alloc(&h->col, sizeof(int) * std::max<int64_t>(h->nnz, 1)));
+    PPCG_HIP(dev_alloc(&h->val64, sizeof(double) * std::max<int64_t>(h->nnz, 1)));
     PPCG_HIP(hipMemcpyAsync(h->rp, rp, sizeof(int) * (h->n + 1), hipMemcpyDeviceToDevice, h->stream));
     PPCG_HIP(hipMemcpyAsync(h->col, ci, sizeof(int) * h->nnz, hipMemcpyDeviceToDevice, h->stream));
     PPCG_HIP(hipMemcpyAsync(h->val64, val, sizeof(double) * h->nnz, hipMemcpyDeviceToDevice, h->stream));
@@ -1541,7 +1667,7 @@ ppcg_status ensure_val32(ppcg_handle *h)
     if (h->val32)
         return PPCG_OK;
     const size_t m = (size_t)std::max<int64_t>(h->nnz_stored, 1);
-    PPCG_HIP(hipMalloc(&h->val32, m * sizeof(float)));
+    PPCG_HIP(dev_alloc(&h->val32, m * sizeof(float)));
     k_convert<float, double><<<blocks_for((size_t)h->nnz_stored, 256), 256, 0, h->stream>>>(
         (size_t)h->nnz_stored, h->val64, h->val32);
     PPCG_HIP(hipGetLastError());
@@ -2950,7 +3076,8 @@ static void destroy_handle(ppcg_handle *h)
     h->fused_arena.release();
     if (h->ev_user)
         (void)hipEventDestroy(h->ev_user);
-    if (h->stream)
+    DevPool *pool = DevPool::use().pool;
+    if (h->stream && !(pool && pool->give_stream(h->stream)))
         (void)hipStreamDestroy(h->stream);
     delete h;
 }
@@ -3012,7 +3139,14 @@ ppcg_status ppcg_create(const ppcg_csr *A, const ppcg_options *opt, void *hip_st
     } while (0)
     CK(hipGetDevice(&h->device));
     CK(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device));
-    CK(hipStreamCreateWithFlags(&h->stream, hipStreamNonBlocking));
+    if (DevPool *pool = DevPool::use().pool)
+        h->stream = pool->take_stream();
+    if (!h->stream)
+        CK(hipStreamCreateWithFlags(&h->stream, hipStreamNonBlocking));
+    struct PoolStream {  // what the creation gives back, it has used on this stream
+        ~PoolStream() { DevPool::use().stream = nullptr; }
+    } pool_stream;
+    DevPool::use().stream = h->stream;
     CK(hipEventCreateWithFlags(&h->ev_user, hipEventDisableTiming));
     hipStream_t s = h->stream;
     CK(hipEventRecord(h->ev_user, h->user_stream));
@@ -3021,9 +3155,9 @@ ppcg_status ppcg_create(const ppcg_csr *A, const ppcg_options *opt, void *hip_st
     const int64_t nnz = A->nnz;
     if (A->mem == PPCG_MEM_HOST) {
         own_csr = true;
-        CK(hipMalloc(&rp, sizeof(int) * (n + 1)));
-        CK(hipMalloc(&ci, sizeof(int) * nnz));
-        CK(hipMalloc(&val, sizeof(double) * nnz));
+        CK(dev_alloc(&rp, sizeof(int) * (n + 1)));
+        CK(dev_alloc(&ci, sizeof(int) * nnz));
+        CK(dev_alloc(&val, sizeof(double) * nnz));
         CK(hipMemcpyAsync(rp, A->row_ptr, sizeof(int) * (n + 1), hipMemcpyHostToDevice, s));
         CK(hipMemcpyAsync(ci, A->col_idx, sizeof(int) * nnz, hipMemcpyHostToDevice, s));
         CK(hipMemcpyAsync(val, A->values, sizeof(double) * nnz, hipMemcpyHostToDevice, s));
@@ -3035,10 +3169,10 @@ ppcg_status ppcg_create(const ppcg_csr *A, const ppcg_options *opt, void *hip_st
         ci = (int *)A->col_idx;
         val = (double *)A->values;
     }
-    CK(hipMalloc(&rowlen, sizeof(int) * n));
-    CK(hipMalloc(&dinv_orig, sizeof(double) * n));
-    CK(hipMalloc(&h->dinv64, sizeof(double) * n));
-    CK(hipMalloc(&err, sizeof(unsigned) * 2));
+    CK(dev_alloc(&rowlen, sizeof(int) * n));
+    CK(dev_alloc(&dinv_orig, sizeof(double) * n));
+    CK(dev_alloc(&h->dinv64, sizeof(double) * n));
+    CK(dev_alloc(&err, sizeof(unsigned) * 2));
     unsigned err_init[2] = {0u, 0xFFFFFFFFu};
     CK(hipMemcpyAsync(err, err_init, sizeof err_init, hipMemcpyHostToDevice, s));
     k_validate<<<blocks_for(n, 256), 256, 0, s>>>(n, nnz, rp, ci, val, dinv_orig, rowlen, err);
