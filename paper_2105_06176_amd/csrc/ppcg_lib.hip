@@ -1198,7 +1198,7 @@ static void shared_for_fused(ppcg_handle *h)
 // half the bytes of the one-byte value indices that the lists replace
 // (or 64 KiB): a wavefront reads them through the scalar cache, and matrices
 // whose chunks are mostly of different kinds gain nothing.
-static ppcg_status build_stencil(ppcg_handle *h)
+static ppcg_status build_stencil(ppcg_handle *h, const int *rp, const int *ci)
 {
     const unsigned fl = h->opt.flags;
     if (h->schunk || h->fmt != FMT_SELL || !h->cpat || h->perm || !h->dinv_const || h->n > kStMaxRows ||
@@ -1233,7 +1233,7 @@ static ppcg_status build_stencil(ppcg_handle *h)
     std::vector<int64_t> cp((size_t)nc + 1);
     unsigned bad = 0u;
     k_fill<unsigned><<<1, 64, 0, s>>>(1, flag, 0u);
-    k_st_scan<<<nc, kSellC, 0, s>>>(nc, h->cptr, h->cpat, h->pats, h->val64, tval, tmask, hash, flag);
+    k_st_scan<<<nc, kSellC, 0, s>>>(h->n, nc, rp, ci, h->cptr, h->cpat, h->pats, h->val64, tval, tmask, hash, flag);
     PPCG_HIP(hipGetLastError());
     PPCG_HIP(hipMemcpyAsync(&bad, flag, sizeof bad, hipMemcpyDeviceToHost, s));
     PPCG_HIP(hipMemcpyAsync(hh.data(), hash, 16 * (size_t)nc, hipMemcpyDeviceToHost, s));
@@ -1530,7 +1530,7 @@ static ppcg_status choose_format(ppcg_handle *h, const int *rp, const int *ci, c
             PPCG_TRY(build_sell(h->stream, h->n, 1, rp, ci, val, rowlen, &sb, shared));
             PPCG_TRY(adopt_sell(h, sb));
             PPCG_TRY(bind_f64(h, dinv_orig));
-            PPCG_TRY(build_stencil(h));
+            PPCG_TRY(build_stencil(h, rp, ci));
             if (h->schunk)
                 return PPCG_OK;
             drop_stencil(h);
@@ -3203,7 +3203,7 @@ ppcg_status ppcg_create(const ppcg_csr *A, const ppcg_options *opt, void *hip_st
     }
     CKS(alloc_f64_vectors(h));
     CKS(choose_format(h, rp, ci, val, rowlen, dinv_orig, rowlen_h));
-    CKS(build_stencil(h));
+    CKS(build_stencil(h, rp, ci));
     CKS(tune_vtab(h, A->mem == PPCG_MEM_HOST ? A->values : nullptr, val));
     CKS(tune_shared(h));
     CKS(tune_form(h));

@@ -47,10 +47,12 @@ __device__ __forceinline__ unsigned long long st_mix(unsigned long long h, unsig
 
 // One wavefront per chunk: the value and the lane mask of every entry of the
 // chunk's list (at cptr[c] / 64 + k), hashes of (offsets, values) and of the
-// masks.  flag[0] |= 1 when an entry holds two different values.  An entry is
-// absent from a row where the stored value is +0.0 (the layout's filler; a
-// stored zero contributes the same nothing).
-__global__ __launch_bounds__(64) void k_st_scan(int nchunks, const int64_t *__restrict__ cptr,
+// masks.  flag[0] |= 1 when an entry holds two different values.  Which rows
+// have an entry comes from their CSR columns, not from the stored values: a
+// zero that the matrix stores is a value like any other (0 * Inf is NaN),
+// where the layout's filler is no entry.
+__global__ __launch_bounds__(64) void k_st_scan(int n, int nchunks, const int *__restrict__ rp,
+                                                const int *__restrict__ ci, const int64_t *__restrict__ cptr,
                                                 const int *__restrict__ cpat, const int *__restrict__ pats,
                                                 const double *__restrict__ val, double *__restrict__ tval,
                                                 unsigned long long *__restrict__ tmask,
@@ -62,13 +64,22 @@ __global__ __launch_bounds__(64) void k_st_scan(int nchunks, const int64_t *__re
     const int64_t base = cptr[c];
     const int len = (int)((cptr[c + 1] - base) / kSellC);
     const int *list = pats + cpat[c];
+    const int p = c * kSellC + l;
+    int e = 0, end = 0;  // this row's entries not yet met
+    if (p < n) {
+        e = rp[p];
+        end = rp[p + 1];
+    }
     unsigned long long hl = st_mix(0x1234567ull, (unsigned)len), hm = st_mix(0x7654321ull, (unsigned)len);
     for (int k = 0; k < len; ++k) {
         const unsigned long long v =
             (unsigned long long)__double_as_longlong(val[(size_t)base + (size_t)k * kSellC + l]);
-        const unsigned long long m = __ballot(v != 0ull);
+        const bool has = e < end && ci[e] == p + list[k];
+        if (has)
+            ++e;
+        const unsigned long long m = __ballot(has);
         const unsigned long long first = m ? __shfl(v, (int)__ffsll((long long)m) - 1, 64) : 0ull;
-        if (__any(v != 0ull && v != first)) {
+        if (__any(has && v != first)) {
             if (l == 0)
                 atomicOr(flag, 1u);
             return;
