@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "ppcg_engine.hpp"
+#include "ppcg_groups.hpp"
 #include "ppcg_kernels.hpp"
 #include "ppcg_pcg.hpp"
 #include "ppcg_small.hpp"
@@ -1241,39 +1242,23 @@ static ppcg_status build_stencil(ppcg_handle *h, const int *rp, const int *ci)
     PPCG_HIP(hipStreamSynchronize(s));
     if (bad)
         return PPCG_OK;
-    std::unordered_map<unsigned long long, int> lists, masks;
-    std::vector<int4> chunk((size_t)nc), items;
-    int64_t nlist = 0, nmask = 0;
-    int longest = 0;
+    ChunkGroups g;
     const int64_t cap = std::max<int64_t>(h->nnz_stored / 2, 65536);
-    for (int c = 0; c < nc; ++c) {
-        const int len = (int)((cp[c + 1] - cp[c]) / kSellC);
-        const auto l = lists.emplace(hh[2 * (size_t)c], (int)nlist);
-        const auto m = masks.emplace(hh[2 * (size_t)c + 1], (int)nmask);
-        if (l.second) {
-            items.push_back(make_int4(c, (int)nlist, 0, 0));
-            nlist += len;
-        }
-        if (m.second) {
-            items.push_back(make_int4(c, (int)nmask, 1, 0));
-            nmask += len;
-        }
-        if (12 * nlist + 8 * nmask > cap)
-            return PPCG_OK;
-        chunk[c] = make_int4(l.first->second, m.first->second, len, 0);
-        longest = std::max(longest, len);
-    }
+    if (!group_chunks(nc, kSellC, cp.data(), hh.data(), cap, &g))
+        return PPCG_OK;
+    const int64_t nlist = g.nlist, nmask = g.nmask;
+    static_assert(sizeof(GroupChunk) == sizeof(int4) && sizeof(GroupItem) == sizeof(int4), "as the device reads them");
     if (!keep)
         PPCG_TRY(h->st_arena.alloc(16 * (size_t)nc + 12 * (size_t)nlist + 8 * (size_t)nmask + 8 * 256));
     int4 *schunk = (int4 *)h->st_arena.take(16 * (size_t)nc);
     h->sval = (double *)h->st_arena.take(8 * (size_t)std::max<int64_t>(nlist, 1));
     h->smask = (unsigned long long *)h->st_arena.take(8 * (size_t)std::max<int64_t>(nmask, 1));
     h->soff = (int *)h->st_arena.take(4 * (size_t)std::max<int64_t>(nlist, 1));
-    hipError_t e = hipMemcpyAsync(schunk, chunk.data(), 16 * (size_t)nc, hipMemcpyHostToDevice, s);
+    hipError_t e = hipMemcpyAsync(schunk, g.chunk.data(), 16 * (size_t)nc, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
-        e = hipMemcpyAsync(items_d, items.data(), 16 * items.size(), hipMemcpyHostToDevice, s);
+        e = hipMemcpyAsync(items_d, g.items.data(), 16 * g.items.size(), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) {
-        k_st_copy<<<(unsigned)items.size(), 64, 0, s>>>(items_d, h->cptr, h->cpat, h->pats, tval, tmask, h->soff,
+        k_st_copy<<<(unsigned)g.items.size(), 64, 0, s>>>(items_d, h->cptr, h->cpat, h->pats, tval, tmask, h->soff,
                                                          h->sval, h->smask);
         k_st_verify<<<nc, 64, 0, s>>>(nc, h->cptr, h->cpat, h->pats, tval, tmask, schunk, h->soff, h->sval,
                                       h->smask, flag);
@@ -1290,7 +1275,7 @@ static ppcg_status build_stencil(ppcg_handle *h, const int *rp, const int *ci)
         h->schunk = schunk;
         h->srun = bad >> 1;
     }
-    h->smaxlen = longest;
+    h->smaxlen = g.longest;
     PPCG_HIP(e);
     return PPCG_OK;
 }
