@@ -337,10 +337,11 @@ ppcg_status ppcg_spmv(ppcg_handle *h, const double *x, double *y);
 /* Describe the stored matrix and the algorithmic byte model. */
 ppcg_status ppcg_get_matrix_info(const ppcg_handle *h, ppcg_matrix_info *mi);
 
-/* Device bytes a handle for an n x n matrix with nnz entries would hold
- * (matrix in its SpMV format with padding estimate, dinv, the eleven solver
- * vectors, b, partials and state; plus the FP32 copy when mixed).  Used for
- * admission by footprint.  Returns 0 for invalid sizes. */
+/* Device bytes a handle for an n x n matrix with nnz entries would hold at
+ * most, by estimate (matrix in its SpMV format with up to half as many entries
+ * again of padding, chunk lists, dinv, the eleven solver vectors, b, partials,
+ * state and the single launch's buffers; plus the FP32 copy when mixed).
+ * Returns 0 for invalid sizes. */
 double ppcg_footprint_bytes(int32_t n, int64_t nnz, ppcg_precision precision);
 
 /* Measure the two kernels of the iteration (Algorithm 2's fused vector
@@ -495,13 +496,15 @@ ppcg_status ppcg_hybrid_solve(ppcg_hybrid *hy, const double *b, const double *x0
 ppcg_status ppcg_hybrid_destroy(ppcg_hybrid *hy); /* NULL-safe */
 
 /* ---------------------------------------------------------------------------
- * Serving: a continuous-batching solve server.  Two threads owned by the
+ * Serving: a continuous-batching solve server.  Threads owned by the
  * server prepare queued requests, taken first-come first-served (matrix
  * copied to the device, validated and laid out, right-hand side staged),
- * and hand them over as they become ready, while the sum
- * of the device footprints (ppcg_footprint_bytes) of the requests it holds
- * stays within the budget, and releases the memory of retired ones; both
- * overlap with the iterations of the active requests.  Prepared requests
+ * and hand them over as they become ready, while the device memory of the
+ * requests it holds (ppcg_footprint_bytes and the copies that a preparation
+ * needs, by estimate, then the bytes that each one holds) and what the server
+ * keeps idle for the next ones stay within the budget, and release the memory
+ * of retired ones; both overlap with the iterations of the active requests.
+ * A request that needs more by that estimate runs alone.  Prepared requests
  * join the batched iteration at the next graph boundary and leave it when
  * they finish, so requests that arrive while others run overlap with them on
  * the device.  Each request's arithmetic is independent of the others in the
@@ -522,7 +525,8 @@ ppcg_status ppcg_srv_create(const ppcg_options *opt, double budget_bytes, ppcg_s
  * was created with PPCG_FLAG_BORROW_INPUTS.  tol: this request's tolerance;
  * precision: any ppcg_precision,
  * PPCG_PRECISION_AUTO included.  *req_id receives the request's id.
- * PPCG_ERR_BUDGET when the request could never fit the budget. */
+ * PPCG_ERR_BUDGET when even a layout with a tenth of padding would not fit the
+ * budget. */
 ppcg_status ppcg_srv_submit(ppcg_server *s, const ppcg_csr *A, const double *b, double tol,
                             ppcg_precision precision, int64_t *req_id);
 

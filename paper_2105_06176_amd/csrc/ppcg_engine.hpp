@@ -12,11 +12,11 @@
 #include <string>
 #include <mutex>
 #include <shared_mutex>
-#include <unordered_map>
 #include <vector>
 
 #include "../../include/ppcg.h"
 #include "ppcg_internal.hpp"
+#include "ppcg_pool.hpp"
 
 namespace ppcg {
 
@@ -41,48 +41,7 @@ void clear_error();
             return s_;                        \
     } while (0)
 
-// ---------------------------------------------------------------- releases
-// Releasing device or pinned host memory synchronizes the whole device, and
-// a device synchronization while another thread captures a graph invalidates
-// that capture.  Every release in the library therefore holds this lock
-// shared, and a graph capture holds it exclusively.
-std::shared_mutex &release_mu();
-
-// Device memory and streams that a server keeps between its requests.  hipFree
-// waits for the whole device, so each of the 20 releases of a request's
-// preparation waited for the iterations of the running ones (a burst of 12
-// requests: 20.5 ms, with the pool 8.9).  A block is taken and given back by the threads that have
-// called `use`; it is given back with no work pending on it (Use::stream, the
-// one that a preparation works on, is synchronized first).  Blocks above
-// kMaxBlock are not kept, idle ones are released beyond the caller's limit
-// (trim), and all of them with the pool.
-class DevPool {
-  public:
-    struct Use {
-        DevPool *pool = nullptr;
-        hipStream_t stream = nullptr;
-    };
-    static Use &use();  // this thread's
-    ~DevPool();
-    hipError_t take(void **p, size_t bytes);
-    void trim(size_t keep);  // idle bytes
-    // NULL stream: none idle
-    hipStream_t take_stream();
-    bool give_stream(hipStream_t s);
-    // of a block of some pool, by any thread; false: no pool's
-    static bool give(void *p);
-
-  private:
-    static constexpr size_t kMaxBlock = (size_t)32 << 20, kMaxIdle = (size_t)256 << 20;
-    static constexpr size_t kMaxStreams = 4;
-    static std::mutex &reg_mu();
-    static std::unordered_map<void *, std::pair<DevPool *, size_t>> &reg();  // blocks of all pools
-    std::mutex mu_;
-    std::multimap<size_t, void *> idle_;
-    size_t idle_bytes_ = 0;
-    std::vector<hipStream_t> streams_;
-};
-
+// ---------------------------------------------------------------- memory
 template <typename T>
 hipError_t dev_alloc(T **p, size_t bytes)
 {
@@ -495,6 +454,9 @@ constexpr int kChunkStep = 32;
 constexpr int kFirstChunk = 32;
 constexpr double kFirstChunkBytes = 30e6;
 double now_ms();
+// Device bytes while a handle is created from host arrays, by estimate
+// (ppcg_footprint_bytes and what its creation holds besides).
+double prepare_bytes(int32_t n, int64_t nnz, ppcg_precision precision);
 // NULL, non-device and too-short device buffers are rejected with a message.
 ppcg_status check_dev_range(const void *p, size_t bytes, const char *what);
 int auto_graph_iters(const ppcg_handle *h);

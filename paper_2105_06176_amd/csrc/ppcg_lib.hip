@@ -24,7 +24,6 @@
 #include <string>
 #include <thread>
 #include <tuple>
-#include <unordered_map>
 #include <vector>
 
 #include "ppcg_engine.hpp"
@@ -40,12 +39,6 @@ namespace ppcg {
 
 // ---------------------------------------------------------------- errors
 static thread_local std::string g_err;
-
-std::shared_mutex &release_mu()
-{
-    static std::shared_mutex m;
-    return m;
-}
 
 void set_error(const char *fmt, ...)
 {
@@ -66,132 +59,6 @@ double now_ms()
 }
 
 static inline unsigned blocks_for(size_t n, unsigned bs) { return (unsigned)((n + bs - 1) / bs); }
-
-// ---------------------------------------------------------------- pool
-DevPool::Use &DevPool::use()
-{
-    static thread_local Use u;
-    return u;
-}
-
-std::mutex &DevPool::reg_mu()
-{
-    static std::mutex m;
-    return m;
-}
-
-std::unordered_map<void *, std::pair<DevPool *, size_t>> &DevPool::reg()
-{
-    static std::unordered_map<void *, std::pair<DevPool *, size_t>> r;
-    return r;
-}
-
-DevPool::~DevPool()
-{
-    trim(0);
-    for (hipStream_t s : streams_)
-        (void)hipStreamDestroy(s);
-    std::lock_guard<std::mutex> lk(reg_mu());
-    for (auto it = reg().begin(); it != reg().end();)  // (blocks still out are released by hipFree)
-        it = it->second.first == this ? reg().erase(it) : std::next(it);
-}
-
-hipError_t DevPool::take(void **p, size_t bytes)
-{
-    size_t size = 512;  // powers of two and the three sizes between them
-    while (size < bytes)
-        size *= 2;
-    if (size > 2048)
-        for (int q = 5; q < 8; ++q)
-            if (size / 8 * q >= bytes) {
-                size = size / 8 * q;
-                break;
-            }
-    if (size > kMaxBlock)
-        return hipMalloc(p, bytes);
-    {
-        std::lock_guard<std::mutex> lk(mu_);
-        auto it = idle_.find(size);
-        if (it != idle_.end()) {
-            *p = it->second;
-            idle_.erase(it);
-            idle_bytes_ -= size;
-            return hipSuccess;
-        }
-    }
-    hipError_t e = hipMalloc(p, size);
-    if (e == hipErrorOutOfMemory) {
-        trim(0);
-        (void)hipGetLastError();
-        e = hipMalloc(p, size);
-    }
-    if (e != hipSuccess)
-        return e;
-    std::lock_guard<std::mutex> lk(reg_mu());
-    reg()[*p] = {this, size};
-    return hipSuccess;
-}
-
-bool DevPool::give(void *p)
-{
-    std::pair<DevPool *, size_t> b;
-    {
-        std::lock_guard<std::mutex> lk(reg_mu());
-        auto it = reg().find(p);
-        if (it == reg().end())
-            return false;
-        b = it->second;
-    }
-    if (use().stream)
-        (void)hipStreamSynchronize(use().stream);
-    std::unique_lock<std::mutex> lk(b.first->mu_);
-    b.first->idle_.emplace(b.second, p);
-    b.first->idle_bytes_ += b.second;
-    lk.unlock();
-    b.first->trim(kMaxIdle);
-    return true;
-}
-
-void DevPool::trim(size_t keep)
-{
-    std::vector<void *> drop;
-    {
-        std::lock_guard<std::mutex> lk(mu_);
-        while (idle_bytes_ > keep) {  // the largest first
-            auto it = std::prev(idle_.end());
-            drop.push_back(it->second);
-            idle_bytes_ -= it->first;
-            idle_.erase(it);
-        }
-    }
-    for (void *p : drop) {
-        {
-            std::lock_guard<std::mutex> lk(reg_mu());
-            reg().erase(p);
-        }
-        std::shared_lock<std::shared_mutex> lk(release_mu());
-        (void)hipFree(p);
-    }
-}
-
-hipStream_t DevPool::take_stream()
-{
-    std::lock_guard<std::mutex> lk(mu_);
-    if (streams_.empty())
-        return nullptr;
-    hipStream_t s = streams_.back();
-    streams_.pop_back();
-    return s;
-}
-
-bool DevPool::give_stream(hipStream_t s)
-{
-    std::lock_guard<std::mutex> lk(mu_);
-    if (streams_.size() >= kMaxStreams)
-        return false;
-    streams_.push_back(s);
-    return true;
-}
 
 // ---------------------------------------------------------------- arena
 ppcg_status DevArena::alloc(size_t bytes)
@@ -559,6 +426,9 @@ static ppcg_status build_sell(hipStream_t s, int n, int sigma, const int *rp, co
     *out = sb;
     return PPCG_OK;
 }
+
+// Stored entries per entry up to which chunk lists are taken untimed.
+constexpr double kListPadding = 1.5;
 
 // ---------------------------------------------------------------- autotuner
 // Candidate SpMV configurations are timed on the matrix itself: five timed
@@ -1503,9 +1373,7 @@ static ppcg_status choose_format(ppcg_handle *h, const int *rp, const int *ci, c
     // and the candidates' SpMV timings, on per-entry columns, say nothing about
     // them.  Per solve, with the timed choice where it fell elsewhere and with
     // the lists: 16^3 125-point 1150, 630 us; 19 x 160 x 90 1510, 910 us.
-    // Up to kListPadding stored entries per entry: rows much shorter than their
-    // chunk's list go on to the timing.
-    constexpr double kListPadding = 1.5;
+    // Rows much shorter than their chunk's list go on to the timing.
     bool unsorted = false;  // the unsorted SELL layout is in place
     if (shared && !forced16 && h->dinv_const && h->opt.precision == PPCG_FP64) {
         int64_t st1 = 0;
@@ -1644,6 +1512,40 @@ static ppcg_status alloc_f64_vectors(ppcg_handle *h)
     h->part = (double *)h->f64.arena.take((size_t)2 * h->ntiles * kPartStride * sizeof(double));
     h->prs = (SysState *)h->f64.arena.take(2 * sizeof(SysState));
     return PPCG_OK;
+}
+
+// Device bytes of a handle with the padding that chunk lists are taken up to.
+static double handle_bytes(int32_t n, int64_t nnz, ppcg_precision precision)
+{
+    const double ntiles = (n + kTileRows - 1) / kTileRows, nchunks = n / kSellC + 2;
+    const double stored = kListPadding * (double)nnz;
+    // stored entries: 8 value + 4 column + 2 (16-bit column offsets, when
+    // built) + 1 (value index, when built) bytes
+    double b = stored * 15.0 + 8.0 * nchunks + 8.0 * n /* dinv */ + 8.0 * n /* perm */ +
+               11.0 * (8.0 * n + kVecPad + 256.0) + 2.0 * ntiles * kPartStride * 8.0 + 24 * 256.0;
+    // the chunks' lists: offsets, and offsets, values and masks with what
+    // found them where that is small (build_stencil)
+    b += 4.0 * nchunks + 4.0 * kMaxSharedOffsets +
+         std::max(std::min(36.0 / kSellC * stored + 64.0 * nchunks, 1048576.0),
+                  16.0 * nchunks + std::max(0.5 * stored, 65536.0)) + 4096.0;
+    // the single launch's records and partial sums, and its second w
+    b += 8.0 * n + ntiles * (2 * 4 * 8.0 + 8.0);
+    if (precision == PPCG_MIXED_FP32)
+        b += stored * 4.0 + 12.0 * (4.0 * n + 256.0) + 2.0 * ntiles * kPartStride * 8.0;
+    if (precision == PPCG_MIXED_FP32_VALUES)
+        b += stored * 4.0;
+    return b;
+}
+
+double prepare_bytes(int32_t n, int64_t nnz, ppcg_precision precision)
+{
+    // beside the handle: the CSR arrays, row lengths and diagonal, and the
+    // layout that a candidate replaces (not yet the 16-bit columns and value
+    // indices of the last one)
+    const double stored = kListPadding * (double)nnz;
+    const double b = handle_bytes(n, nnz, precision) + 12.0 * nnz + 16.0 * n + 9.0 * stored + 8.0 * n + 16 * 512.0;
+    // a pool rounds up by a quarter at most, and only blocks of 32 MiB and less
+    return b + 0.25 * std::min(b, 20 * 33554432.0);
 }
 
 // FP32 copy of the stored matrix values (both mixed modes).
@@ -3396,7 +3298,9 @@ ppcg_status ppcg_get_matrix_info(const ppcg_handle *h, ppcg_matrix_info *mi)
                        (h->fmt == FMT_SELL ? 8.0 * (h->nchunks + 1) : 4.0 * (h->n + 1)) +
                        (h->perm ? 8.0 * h->n : 0.0) + (h->col16 ? 2.0 * (double)h->nnz_stored : 0.0) +
                        (h->vidx ? (double)h->nnz_stored + 8.0 * h->nvtab : 0.0) +
-                       (h->cpat ? 4.0 * (h->nchunks + h->npats) : 0.0) + (double)h->st_arena.size;
+                       (h->cpat ? 4.0 * (h->nchunks + h->npats) : 0.0) + (double)h->st_arena.size +
+                       (double)h->fused_arena.size + (h->val32 ? 4.0 * (double)h->nnz_stored : 0.0) +
+                       (h->plain_desc ? sizeof(SysDesc) + sizeof(SysState) + 8.0 * h->ntiles + 12.0 : 0.0);
     mi->setup_ms = h->setup_ms;
     mi->col_index_bytes =
         h->shared_on ? 0
@@ -3415,19 +3319,7 @@ ppcg_status ppcg_get_matrix_info(const ppcg_handle *h, ppcg_matrix_info *mi)
 
 double ppcg_footprint_bytes(int32_t n, int64_t nnz, ppcg_precision precision)
 {
-    if (n < 1 || nnz < n)
-        return 0.0;
-    const double ntiles = (n + kTileRows - 1) / kTileRows;
-    const double stored = 1.10 * (double)nnz;  // padding allowance
-    // stored entries: 8 value + 4 column + 2 (16-bit column offsets, when
-    // built) + 1 (value index, when built) bytes
-    double b = stored * 15.0 + 8.0 * (n / kSellC + 2) + 8.0 * n /* dinv */ + 8.0 * n /* perm */ +
-               11.0 * 8.0 * n + 2.0 * ntiles * kPartStride * 8.0 + 12 * 256.0;
-    if (precision == PPCG_MIXED_FP32)
-        b += stored * 4.0 + 12.0 * 4.0 * n + 2.0 * ntiles * kPartStride * 8.0;
-    if (precision == PPCG_MIXED_FP32_VALUES)
-        b += stored * 4.0;
-    return b;
+    return n < 1 || nnz < n ? 0.0 : handle_bytes(n, nnz, precision);
 }
 
 ppcg_status ppcg_time_kernels(ppcg_handle *h, const double *b, int32_t iters, double *ms_vma, double *ms_spmv)

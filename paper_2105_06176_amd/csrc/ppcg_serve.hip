@@ -1,7 +1,7 @@
 // ppcg_serve.hip -- continuous-batching solve server (ppcg_srv_* in ppcg.h).
 //
 // Requests queue on the host.  Preparation threads owned by the server take
-// them first-come first-served while the sum of the device footprints of the
+// them first-come first-served while the sum of the device memory of the
 // requests the server holds (in preparation, prepared, or on the device)
 // stays within the budget, and prepare each one on a stream of its own: the
 // matrix is copied to the device, validated and laid out (ppcg_create) and
@@ -68,7 +68,7 @@ enum ReqState { RQ_QUEUED, RQ_PREPARING, RQ_PREPARED, RQ_ACTIVE, RQ_FINISHING, R
 struct Request {
     int64_t id = 0;
     ReqState state = RQ_QUEUED;
-    double footprint = 0.0;
+    double footprint = 0.0;  // device bytes: reserved for its preparation, then those it holds
     double tol = 0.0;
     ppcg_precision precision = PPCG_FP64;
     ppcg_method method = PPCG_METHOD_PIPECG;
@@ -126,9 +126,24 @@ struct ppcg_server {
     std::vector<std::thread> prep;
 };
 
+// Device bytes that a request holds at least: its matrix with a tenth of
+// padding, dinv, the row order, the vectors and their partial sums.
+static double least_bytes(int32_t n, int64_t nnz, ppcg_precision precision)
+{
+    const double parts = 2.0 * ((n + kTileRows - 1) / kTileRows) * kPartStride * 8.0, stored = 1.10 * (double)nnz;
+    double b = stored * 15.0 + 8.0 * (n / kSellC + 2) + 104.0 * n + parts + 12 * 256.0;
+    if (precision != PPCG_FP64)
+        b += stored * 4.0;
+    if (precision == PPCG_MIXED_FP32)
+        b += 48.0 * n + parts;
+    return b;
+}
+
 // A preparation thread may take the first queued request: within the slot
 // count, and within the budget unless nothing else holds device memory (a
-// retired request holds its memory until it is released).
+// retired request holds its memory until it is released).  What a
+// preparation needs at most is reserved for it; a prepared request counts
+// with the blocks it holds.
 static bool can_prepare(const ppcg_server *s)
 {
     if (s->stop || s->prep_rc != PPCG_OK || s->queue.empty())
@@ -183,7 +198,7 @@ static ppcg_status prepare(ppcg_server *s, Request &r)
 static void prep_loop(ppcg_server *s)
 {
     const bool dev_ok = hipSetDevice(s->device) == hipSuccess;
-    DevPool::use() = {&s->pool, nullptr};
+    DevPool::use().pool = &s->pool;
     std::unique_lock<std::mutex> lk(s->mu);
     if (!dev_ok) {
         s->prep_rc = PPCG_ERR_DEVICE;
@@ -251,14 +266,17 @@ static void prep_loop(ppcg_server *s)
         r.state = RQ_PREPARING;
         s->used += r.footprint;
         ++s->preparing;
-        const double spare = s->budget - s->used;
         lk.unlock();
-        s->pool.trim(spare > 0.0 ? (size_t)std::min(spare, 1e15) : 0);  // the budget holds for idle blocks too
+        DevPool::use().bytes = 0;
         const ppcg_status rc = prepare(s, r);
         std::string msg = rc == PPCG_OK ? std::string() : std::string(ppcg_last_error());
         lk.lock();
         --s->preparing;
         if (r.h) {
+            const double held = (double)DevPool::use().bytes;
+            s->used += held - r.footprint;
+            r.footprint = held;
+            s->prep_cv.notify_all();  // more than it holds was reserved
             r.state = RQ_PREPARED;
             s->ready.push_back(id);
         } else {
@@ -337,7 +355,7 @@ static ppcg_status retire_finished(ppcg_server *s)
         if (rerun) {
             r.precision = PPCG_FP64;
             r.method = s->defaults.method;
-            r.footprint = ppcg_footprint_bytes(r.n, r.nnz, PPCG_FP64);
+            r.footprint = prepare_bytes(r.n, r.nnz, PPCG_FP64);
         }
     }
     if (!s->retired.empty()) {
@@ -374,6 +392,7 @@ ppcg_status ppcg_srv_create(const ppcg_options *opt, double budget_bytes, ppcg_s
         budget_bytes = 0.8 * (double)fr;
     }
     s->budget = budget_bytes;
+    s->pool.set_limit((size_t)std::min(budget_bytes, 1e18));
     PPCG_HIP(hipGetDevice(&s->device));
     PPCG_HIP(hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking));
     s->eng.reset(new Engine(s->stream));
@@ -441,7 +460,9 @@ ppcg_status ppcg_srv_submit(ppcg_server *s, const ppcg_csr *A, const double *b, 
             precision = PPCG_FP64;
         }
     }
-    const double fp = ppcg_footprint_bytes(A->n, A->nnz, precision);
+    // (one that is prepared only with nothing else on the device, because its
+    // estimate passes the budget, is not refused)
+    const double fp = least_bytes(A->n, A->nnz, precision);
     if (fp > s->budget) {
         set_error("request footprint %.0f bytes exceeds the budget %.0f", fp, s->budget);
         return PPCG_ERR_BUDGET;
@@ -449,7 +470,7 @@ ppcg_status ppcg_srv_submit(ppcg_server *s, const ppcg_csr *A, const double *b, 
     Request r;
     std::unique_lock<std::mutex> lk(s->mu);
     r.id = s->next_id++;
-    r.footprint = fp;
+    r.footprint = prepare_bytes(A->n, A->nnz, precision);
     r.tol = tol;
     r.precision = precision;
     r.method = method;
