@@ -141,6 +141,13 @@ struct ByteModel {
     double vma, spmv;
 };
 
+// Whether the iteration's SpMV reads the chunk lists: all but PIPECG with FP32
+// values, which streams those.
+static bool reads_lists(const ppcg_handle *h, bool pcg, int prec)
+{
+    return h->schunk && (pcg || prec == PREC_F64);
+}
+
 static ByteModel byte_model(const ppcg_handle *h, int prec)
 {
     const double ve = prec == PREC_F32 ? 4.0 : 8.0;   // vector element
@@ -163,7 +170,7 @@ static ByteModel byte_model(const ppcg_handle *h, int prec)
     const double ie = sh ? 0.0 : (h->col16 && (PPCG_PCG_V32_COL16 || !(pcg && prec == PREC_V32))) ? 2.0 : 4.0;
     bm.spmv = (me + ie) * (double)h->nnz + ptr + (sh ? 4.0 * h->nchunks : 0.0) + (pcg ? 4.0 : 2.0) * ve * n;
     // on chunk lists 16 bytes per chunk stand for the matrix
-    if (h->schunk)
+    if (reads_lists(h, pcg, prec))
         bm.spmv = 16.0 * h->nchunks + (pcg ? 4.0 : 2.0) * ve * n;
     // the single-launch form keeps n in registers (neither written by the
     // SpMV nor read by the update) and, with a constant diagonal, forms
