@@ -241,15 +241,18 @@ typedef struct {
                                 every SELL column fits a 16-bit offset from its row, 0 when the
                                 PIPECG SpMV with FP64 vectors reads the chunks' shared offset
                                 lists (PPCG_FLAG_SELL_SHARED_OFFSETS), else 4.  0 and a
-                                value_bytes of 1 also stand for the single-launch form of
-                                constant-coefficient stencils, which reads lists of offsets,
-                                values and row masks per 64 rows and nothing per entry
-                                (bytes_per_iter counts that) */
+                                value_bytes of 1 also stand for the chunk lists of
+                                constant-coefficient stencils (offsets, values and row masks
+                                per 64 rows, nothing per entry; bytes_per_iter counts that),
+                                which FP64 PIPECG and classic PCG read */
     int32_t diag_const;      /* 1: every diagonal entry is equal; the fused update then reads
                                 the inverse diagonal as one cached value, not a vector */
     int32_t value_bytes;     /* bytes per stored value the iteration's SpMV reads: 1 with the
-                                value table (FP64 PIPECG), 4 with FP32 values, else 8 */
-    int32_t distinct_values; /* entries of the value table (0 when there is none) */
+                                value table (FP64 PIPECG) or on chunk lists (FP64), 4 with
+                                FP32 values, else 8 */
+    int32_t distinct_values; /* distinct values of the value table or of the chunk lists, the
+                                padding's 0.0 included (0 when there is neither, or more
+                                than 256) */
     int32_t iter_launches;   /* launches per iteration of the handle's current method and
                                 precision: 1 for FP64 PIPECG in the single-launch form
                                 (bytes_per_iter then omits n's write and read, 16 bytes per

@@ -1143,9 +1143,14 @@ static ppcg_status build_stencil(ppcg_handle *h, const int *rp, const int *ci)
     }
     if (e == hipSuccess)
         e = hipMemcpyAsync(&bad, flag, sizeof bad, hipMemcpyDeviceToHost, s);
+    std::vector<double> values((size_t)nlist);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(values.data(), h->sval, 8 * (size_t)nlist, hipMemcpyDeviceToHost, s);
     const hipError_t es = hipStreamSynchronize(s);
     if (e == hipSuccess)
         e = es;
+    ValueSet distinct;
+    h->st_distinct = distinct.add(0) && distinct.scan(values.data(), nlist) ? distinct.count : 0;
     if (e != hipSuccess || (bad & 1u)) {  // two different lists of one hash
         drop_stencil(h);
     } else {
@@ -3309,17 +3314,17 @@ ppcg_status ppcg_get_matrix_info(const ppcg_handle *h, ppcg_matrix_info *mi)
                        (double)h->fused_arena.size + (h->val32 ? 4.0 * (double)h->nnz_stored : 0.0) +
                        (h->plain_desc ? sizeof(SysDesc) + sizeof(SysState) + 8.0 * h->ntiles + 12.0 : 0.0);
     mi->setup_ms = h->setup_ms;
+    const bool pcg = h->opt.method == PPCG_METHOD_PCG || h->opt.precision == PPCG_MIXED_FP32;
+    const bool values32 = h->opt.precision == PPCG_MIXED_FP32 || h->opt.precision == PPCG_MIXED_FP32_VALUES;
+    const bool lists = reads_lists(h, pcg, values32 ? PREC_V32 : PREC_F64);
     mi->col_index_bytes =
-        h->shared_on ? 0
+        h->shared_on || lists ? 0
         : (h->col16 && (PPCG_PCG_V32_COL16 ||
                         !(h->opt.method == PPCG_METHOD_PCG && h->opt.precision == PPCG_MIXED_FP32_VALUES))) ? 2
                                                                                                              : 4;
     mi->diag_const = h->dinv_const ? 1 : 0;
-    const bool pcg = h->opt.method == PPCG_METHOD_PCG || h->opt.precision == PPCG_MIXED_FP32;
-    mi->value_bytes = h->opt.precision == PPCG_MIXED_FP32 || h->opt.precision == PPCG_MIXED_FP32_VALUES ? 4
-                      : ((h->vidx || h->schunk) && !pcg)                                                              ? 1
-                                                                                                       : 8;
-    mi->distinct_values = h->nvtab;
+    mi->value_bytes = values32 ? 4 : lists || (h->vidx && !pcg) ? 1 : 8;
+    mi->distinct_values = h->vidx ? h->nvtab : h->schunk ? h->st_distinct : 0;
     mi->iter_launches = (h->form == FORM_FUSED && !pcg && h->opt.precision == PPCG_FP64) ? 1 : 2;
     return PPCG_OK;
 }

@@ -42,3 +42,14 @@ def test_fp64_reads_the_lists(gen):
     mi = info(A)
     assert mi["iter_launches"] == 1
     assert mi["bytes_spmv"] == 16.0 * ((A.n + 63) // 64) + 8.0 * A.n  # n stays in registers
+
+
+@pytest.mark.parametrize("gen", GENS)
+def test_reported_values_of_list_matrices(gen):
+    """The diagonal, -1 and the padding's 0.0; no bytes per value in FP64 by either method."""
+    A = gen()
+    for options in ({}, {"flags": ppcg.FLAG_SELL_VALUE_TABLE}, {"method": "pcg"}):
+        mi = info(A, **options)
+        assert (mi["distinct_values"], mi["value_bytes"], mi["col_index_bytes"]) == (3, 1, 0), options
+    mi = info(A, flags=ppcg.FLAG_SELL_FULL_VALUES)
+    assert (mi["distinct_values"], mi["value_bytes"]) == (0, 8)
