@@ -131,6 +131,7 @@ struct ppcg_handle {
     int st_distinct = 0;  // distinct values of the lists and 0.0 (0: more than kMaxValueTable)
     int srun = 0;  // some chunk's list is runs of consecutive columns
     ppcg::DevArena st_arena;
+    bool st_refused = false;  // its unsorted chunks do not qualify
     int *perm = nullptr, *invperm = nullptr;
     double *val64 = nullptr;  // FP64 values in the stored format
     float *val32 = nullptr;   // FP32 copy of the stored values (mixed modes)

@@ -1081,7 +1081,7 @@ static ppcg_status build_stencil(ppcg_handle *h, const int *rp, const int *ci)
     const unsigned fl = h->opt.flags;
     if (h->schunk || h->fmt != FMT_SELL || !h->cpat || h->perm || !h->dinv_const || h->n > kStMaxRows ||
         (fl & (PPCG_FLAG_SELL_COL16 | PPCG_FLAG_SELL_COL32 | PPCG_FLAG_SELL_NO_SHARED_OFFSETS |
-               PPCG_FLAG_SELL_FULL_VALUES | PPCG_FLAG_ITER_TWO_LAUNCH)) != 0)
+               PPCG_FLAG_SELL_FULL_VALUES | PPCG_FLAG_ITER_TWO_LAUNCH)) != 0 || h->st_refused)
         return PPCG_OK;
     hipStream_t s = h->stream;
     const int nc = h->nchunks;
@@ -1095,8 +1095,16 @@ static ppcg_status build_stencil(ppcg_handle *h, const int *rp, const int *ci)
     DevArena tmp;
     struct Free {
         DevArena &a;
-        ~Free() { a.release(); }
-    } free_tmp{tmp};
+        ppcg_handle *h;
+        ~Free()
+        {
+            a.release();
+            if (!h->schunk) {  // refused: nothing stays, and the layout is not scanned again
+                drop_stencil(h);
+                h->st_refused = true;
+            }
+        }
+    } free_tmp{tmp, h};
     const size_t scratch = 16 * (size_t)nl + (16 + 32) * (size_t)nc + 8 * 256;
     const size_t most = 16 * (size_t)nc + 20 * (size_t)nl + 8 * 256;
     const bool keep = scratch + most <= (1u << 20);
@@ -1151,9 +1159,7 @@ static ppcg_status build_stencil(ppcg_handle *h, const int *rp, const int *ci)
         e = es;
     ValueSet distinct;
     h->st_distinct = distinct.add(0) && distinct.scan(values.data(), nlist) ? distinct.count : 0;
-    if (e != hipSuccess || (bad & 1u)) {  // two different lists of one hash
-        drop_stencil(h);
-    } else {
+    if (e == hipSuccess && !(bad & 1u)) {  // (else two different lists of one hash)
         h->schunk = schunk;
         h->srun = bad >> 1;
     }
@@ -1398,7 +1404,6 @@ static ppcg_status choose_format(ppcg_handle *h, const int *rp, const int *ci, c
             PPCG_TRY(build_stencil(h, rp, ci));
             if (h->schunk)
                 return PPCG_OK;
-            drop_stencil(h);
             unsorted = true;
         }
     }
