@@ -555,13 +555,14 @@ ppcg_status ensure_fused(ppcg_handle *h)
     if (h->frec)
         return PPCG_OK;
     const size_t nft = (size_t)fused_tiles(h);
-    const size_t pb = 2 * nft * 4 * sizeof(double), vb = (size_t)h->n * sizeof(double);
+    const size_t pb = 2 * nft * 4 * sizeof(double);
+    const size_t vb = h->schunk ? 0 : (size_t)h->n * sizeof(double);  // (k_stencil gathers from w and u)
     const size_t hb = 2 * kStHist * sizeof(double);
     PPCG_TRY(h->fused_arena.alloc(2 * sizeof(SysState) + hb + pb + vb + 4 * 256));
     h->frec = (SysState *)h->fused_arena.take(2 * sizeof(SysState));
     h->shist = (double *)h->fused_arena.take(hb);
     h->fpart = (double *)h->fused_arena.take(pb);
-    h->w1 = (double *)h->fused_arena.take(vb);
+    h->w1 = vb ? (double *)h->fused_arena.take(vb) : nullptr;
     return PPCG_OK;
 }
 
