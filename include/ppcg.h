@@ -508,7 +508,9 @@ ppcg_status ppcg_hybrid_destroy(ppcg_hybrid *hy); /* NULL-safe */
  * keeps idle for the next ones stay within the budget, and release the memory
  * of retired ones; both overlap with the iterations of the active requests.
  * A request that needs more by that estimate runs alone.  Prepared requests
- * join the batched iteration at the next graph boundary and leave it when
+ * join the batched iteration at the next graph boundary (large ones in turn,
+ * as far as one iteration of all of them fits the memory-side cache; smaller
+ * ones pass those that wait) and leave it when
  * they finish, so requests that arrive while others run overlap with them on
  * the device.  Each request's arithmetic is independent of the others in the
  * mix: its result is bitwise identical to a solo ppcg_solve of the same

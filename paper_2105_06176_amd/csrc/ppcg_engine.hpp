@@ -458,6 +458,8 @@ double now_ms();
 // Device bytes while a handle is created from host arrays, by estimate
 // (ppcg_footprint_bytes and what its creation holds besides).
 double prepare_bytes(int32_t n, int64_t nnz, ppcg_precision precision);
+// Bytes that one iteration of a handle moves, by the byte model (mixed: MixKind).
+double iter_bytes(const ppcg_handle *h, int mixed);
 // NULL, non-device and too-short device buffers are rejected with a message.
 ppcg_status check_dev_range(const void *p, size_t bytes, const char *what);
 int auto_graph_iters(const ppcg_handle *h);

@@ -188,6 +188,12 @@ static ByteModel byte_model(const ppcg_handle *h, int prec)
     return bm;
 }
 
+double iter_bytes(const ppcg_handle *h, int mixed)
+{
+    const ByteModel bm = byte_model(h, mixed == MIX_INNER32 ? PREC_F32 : mixed == MIX_VALUES32 ? PREC_V32 : PREC_F64);
+    return bm.vma + bm.spmv;
+}
+
 // ---------------------------------------------------------------- SELL build
 struct SellBuild {
     int sigma = 1;
@@ -2244,8 +2250,7 @@ ppcg_status Engine::add(ppcg_handle *h, int mixed, double tol, const double *, i
     j.mixed = mixed;
     j.tol = tol;
     j.x0_zero = h->x0_zero;
-    const ByteModel bm = byte_model(h, mixed == MIX_INNER32 ? PREC_F32 : mixed == MIX_VALUES32 ? PREC_V32 : PREC_F64);
-    j.iter_bytes = bm.vma + bm.spmv;
+    j.iter_bytes = iter_bytes(h, mixed);
     j.t_start = now_ms();
     const ppcg_options &o = h->opt;
     const int stop = o.stop == PPCG_STOP_PRECOND_ABS ? STOP_ABS : STOP_REL;

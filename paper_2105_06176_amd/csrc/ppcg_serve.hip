@@ -44,8 +44,11 @@ constexpr int kServerSlots = 1024;
 #define PPCG_SERVE_GRAPH_ITERS 8
 #endif
 constexpr int kServeGraphIters = PPCG_SERVE_GRAPH_ITERS;
-// ... with no request left to join (a burst of 12: 8.4 ms with 8, 8.0 with 16, 7.7 with 32)
+// ... with no request left to join (a burst of 12: 8.4 ms with 8, 8.0 with 16,
+// 7.7 with 32), up to kServeLastBytes moved in the chunk, about 1 ms: a request
+// that arrives meanwhile waits for the chunk
 constexpr int kServeLastIters = 32;
+constexpr double kServeLastBytes = 5e9;
 // preparation threads: requests are prepared concurrently (copy, validation,
 // layout and staging), taken first come first served, admitted as they
 // become ready (a burst of 12 with 2, 3, 4 and 6 threads: 8.1, 7.5, 7.0, 6.8 ms)
@@ -53,6 +56,17 @@ constexpr int kServeLastIters = 32;
 #define PPCG_SERVE_PREP_THREADS 4
 #endif
 constexpr int kPrepThreads = PPCG_SERVE_PREP_THREADS;
+// Large requests, whose iteration moves kLargeBytes and more, iterate together
+// only as far as one pass over them fits the memory-side cache: past it each
+// evicts the others' vectors, and all finish late.  Smaller ones pass a large
+// one that waits.  Prepared ahead: at most kReadyMost.  800 requests at once
+// (1,000 to 4 M rows), solves/s: all admitted (36 to 55 at a time) 80 to 83,
+// with 2 preparation threads (9 at a time) 93; in turn with 128 MB 102, 250 MB
+// 106, 400 MB 103, 1 GB 83; 16 prepared ahead 104.  At 66 requests/s the 99th
+// percentile went from 204 to 166 ms.
+constexpr double kActiveBytes = kCacheBytes;
+constexpr double kLargeBytes = kActiveBytes / 16;
+constexpr int kReadyMost = kPrepThreads + 2;
 // automatic precision: smallest systems given reduced precision
 #ifndef PPCG_AUTO_VALUES32_ROWS
 #define PPCG_AUTO_VALUES32_ROWS 65536
@@ -82,6 +96,7 @@ struct Request {
     const double *val_p = nullptr, *b_p = nullptr;
     ppcg_handle *h = nullptr;
     int job = -1;
+    double iter_bytes = 0.0;  // that its iteration moves, once active
     ppcg_info info{};
 };
 
@@ -120,6 +135,8 @@ struct ppcg_server {
     double used = 0.0;          // footprints of the handles in preparation, prepared, active or retired
     int preparing = 0;
     int active = 0;
+    double active_bytes = 0.0;  // that one iteration of the active requests moves
+    double large_bytes = 0.0;   // ... of the large ones
     bool stop = false;
     ppcg_status prep_rc = PPCG_OK;  // a device error met while preparing, reported by the next step
     std::string prep_msg;
@@ -140,7 +157,7 @@ static double least_bytes(int32_t n, int64_t nnz, ppcg_precision precision)
 }
 
 // A preparation thread may take the first queued request: within the slot
-// count, and within the budget unless nothing else holds device memory (a
+// count, not too far ahead of the admissions, and within the budget unless nothing else holds device memory (a
 // retired request holds its memory until it is released).  What a
 // preparation needs at most is reserved for it; a prepared request counts
 // with the blocks it holds.
@@ -149,7 +166,7 @@ static bool can_prepare(const ppcg_server *s)
     if (s->stop || s->prep_rc != PPCG_OK || s->queue.empty())
         return false;
     const int held = s->active + (int)s->ready.size() + s->preparing;
-    if (held >= kServerSlots)
+    if (held >= kServerSlots || (int)s->ready.size() + s->preparing >= kReadyMost)
         return false;
     const Request &r = s->reqs.at(s->queue.front());
     return (held == 0 && s->finishing == 0) || s->used + r.footprint <= s->budget;
@@ -293,15 +310,34 @@ static void prep_loop(ppcg_server *s)
     }
 }
 
-// Admit the prepared requests (calling thread, under `mu`).
+static void count_active(ppcg_server *s, const Request &r, int sign)
+{
+    s->active += sign;
+    s->active_bytes += sign * r.iter_bytes;
+    if (r.iter_bytes >= kLargeBytes)
+        s->large_bytes += sign * r.iter_bytes;
+}
+
+// Admit the prepared requests (calling thread, under `mu`): the large ones in
+// the order they became ready, as far as they fit (one always does).
 static ppcg_status admit(ppcg_server *s)
 {
-    while (!s->ready.empty()) {
-        Request &r = s->reqs.at(s->ready.front());
-        s->ready.pop_front();
+    bool waits = false;  // a large one
+    for (size_t k = 0; k < s->ready.size();) {
+        Request &r = s->reqs.at(s->ready[k]);
         const int mixed = r.precision == PPCG_MIXED_FP32          ? MIX_INNER32
                           : r.precision == PPCG_MIXED_FP32_VALUES ? MIX_VALUES32
                                                                   : MIX_NONE;
+        r.iter_bytes = iter_bytes(r.h, mixed);
+        if (r.iter_bytes >= kLargeBytes) {
+            waits = waits || (s->large_bytes > 0.0 && s->large_bytes + r.iter_bytes > kActiveBytes);
+            if (waits) {
+                ++k;
+                continue;
+            }
+        }
+        s->ready.erase(s->ready.begin() + k);
+        s->prep_cv.notify_one();  // to prepare another one
         ppcg_status rc = s->eng->add(r.h, mixed, r.tol, nullptr, &r.job);
         if (rc != PPCG_OK) {
             ppcg_destroy(r.h);
@@ -315,7 +351,7 @@ static ppcg_status admit(ppcg_server *s)
             return rc;
         }
         r.state = RQ_ACTIVE;
-        ++s->active;
+        count_active(s, r, 1);
         // inputs now live on the device (kept while a fallback rerun may need them)
         if (!(r.auto_prec && r.precision != PPCG_FP64)) {
             std::vector<int32_t>().swap(r.rp);
@@ -350,7 +386,7 @@ static ppcg_status retire_finished(ppcg_server *s)
         s->retired.push_back({kv.first, r.h, r.footprint, rerun});
         r.h = nullptr;
         r.state = RQ_FINISHING;
-        --s->active;
+        count_active(s, r, -1);
         ++s->finishing;
         if (rerun) {
             r.precision = PPCG_FP64;
@@ -520,7 +556,9 @@ ppcg_status ppcg_srv_step(ppcg_server *s, int32_t *active, int32_t *queued)
     if (s->active > 0) {
         // the engine and the active requests belong to this thread
         const bool none_waits = s->queue.empty() && s->ready.empty() && s->preparing == 0;
-        const int chunk = none_waits ? kServeLastIters : kServeGraphIters;
+        int chunk = kServeGraphIters;
+        while (none_waits && chunk < kServeLastIters && 2 * chunk * s->active_bytes <= kServeLastBytes)
+            chunk *= 2;
         lk.unlock();
         PPCG_TRY(s->eng->step(chunk));
         lk.lock();
