@@ -346,8 +346,9 @@ __device__ __forceinline__ double pcg_spmv_tile(const SysDesc &d, const WorkItem
         // 16-bit columns measured slower for FP32 values with FP64
         // vectors (27-point case, 263 vs 242 ms), so that mix reads 32-bit ones
         const bool c16 = d.col16 && (PPCG_PCG_V32_COL16 || !(sizeof(T) == 8 && sizeof(VT) == 4));
-        const StBuf ub = __builtin_amdgcn_make_buffer_rsrc((void *)U, 0, n * (int)sizeof(T), 0x00020000);
-        const StBuf pb = __builtin_amdgcn_make_buffer_rsrc((void *)Pold, 0, n * (int)sizeof(T), 0x00020000);
+        const int bytes = (int)((unsigned)n * (unsigned)sizeof(T));  // (lists have at most kStMaxRows rows)
+        const StBuf ub = __builtin_amdgcn_make_buffer_rsrc((void *)U, 0, bytes, 0x00020000);
+        const StBuf pb = __builtin_amdgcn_make_buffer_rsrc((void *)Pold, 0, bytes, 0x00020000);
 #pragma unroll 1
         for (int c0 = row0 + wave * kSellC; c0 < row1; c0 += kSpmvThreads) {
             const int chunk = c0 / kSellC, i = c0 + lane;
