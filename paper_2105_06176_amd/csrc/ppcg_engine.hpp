@@ -128,7 +128,7 @@ struct ppcg_handle {
     double *sval = nullptr;
     unsigned long long *smask = nullptr;
     int smaxlen = 0;
-    int st_distinct = 0;  // distinct values of the lists and 0.0 (0: more than kMaxValueTable)
+    int64_t snlist = 0;  // entries of soff and sval
     int srun = 0;  // some chunk's list is runs of consecutive columns
     ppcg::DevArena st_arena;
     bool st_refused = false;  // its unsorted chunks do not qualify

@@ -1158,19 +1158,15 @@ static ppcg_status build_stencil(ppcg_handle *h, const int *rp, const int *ci)
     }
     if (e == hipSuccess)
         e = hipMemcpyAsync(&bad, flag, sizeof bad, hipMemcpyDeviceToHost, s);
-    std::vector<double> values((size_t)nlist);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(values.data(), h->sval, 8 * (size_t)nlist, hipMemcpyDeviceToHost, s);
     const hipError_t es = hipStreamSynchronize(s);
     if (e == hipSuccess)
         e = es;
-    ValueSet distinct;
-    h->st_distinct = distinct.add(0) && distinct.scan(values.data(), nlist) ? distinct.count : 0;
     if (e == hipSuccess && !(bad & 1u)) {  // (else two different lists of one hash)
         h->schunk = schunk;
         h->srun = bad >> 1;
     }
     h->smaxlen = g.longest;
+    h->snlist = nlist;
     PPCG_HIP(e);
     return PPCG_OK;
 }
@@ -3334,7 +3330,15 @@ ppcg_status ppcg_get_matrix_info(const ppcg_handle *h, ppcg_matrix_info *mi)
                                                                                                              : 4;
     mi->diag_const = h->dinv_const ? 1 : 0;
     mi->value_bytes = values32 ? 4 : lists || (h->vidx && !pcg) ? 1 : 8;
-    mi->distinct_values = h->vidx ? h->nvtab : h->schunk ? h->st_distinct : 0;
+    mi->distinct_values = h->nvtab;
+    if (h->schunk && !h->vidx) {
+        std::vector<double> values((size_t)h->snlist);
+        PPCG_HIP(hipMemcpyAsync(values.data(), h->sval, sizeof(double) * values.size(), hipMemcpyDeviceToHost,
+                                h->stream));
+        PPCG_HIP(hipStreamSynchronize(h->stream));
+        ValueSet distinct;
+        mi->distinct_values = distinct.add(0) && distinct.scan(values.data(), h->snlist) ? distinct.count : 0;
+    }
     mi->iter_launches = (h->form == FORM_FUSED && !pcg && h->opt.precision == PPCG_FP64) ? 1 : 2;
     return PPCG_OK;
 }
