@@ -267,6 +267,42 @@ __global__ __launch_bounds__(64) void k_sell_union_count(int n, int nchunks, con
         cnt[c] = k > cap ? -1 : k;
 }
 
+// Looks at gridDim.x chunks spread over the matrix: flag[1] = 1 where the rows
+// of one hold two values at one offset, or its merged list passes the cap above
+// (then no chunk lists describe the matrix, ppcg_stencil.hpp).  Nothing to look
+// at where flag[0] says that the diagonal varies.
+__global__ __launch_bounds__(64) void k_list_sample(int n, int nchunks, const int *__restrict__ rp,
+                                                    const int *__restrict__ ci, const double *__restrict__ val,
+                                                    unsigned *__restrict__ flag)
+{
+    if (flag[0])
+        return;
+    const int c = (int)((long long)nchunks * blockIdx.x / gridDim.x), l = threadIdx.x;
+    const int p = c * kSellC + l;
+    int e = 0, end = 0;
+    if (p < n) {
+        e = rp[p];
+        end = rp[p + 1];
+    }
+    const int cap = 2 * -wave_min_i32(e - end) + 2;
+    for (int k = 0;; ++k) {
+        const int off = e < end ? ci[e] - p : INT_MAX;
+        const int m = wave_min_i32(off);
+        if (m == INT_MAX)
+            return;
+        const bool has = off == m;
+        const unsigned long long v = has ? (unsigned long long)__double_as_longlong(val[e]) : 0ull;
+        const unsigned long long first = __shfl(v, (int)__ffsll((long long)__ballot(has)) - 1, 64);
+        if (k == cap || __any(has && v != first)) {
+            if (l == 0)
+                flag[1] = 1u;
+            return;
+        }
+        if (has)
+            ++e;
+    }
+}
+
 // k_sell_union: the merged list of chunk c (len = its stored slots, from
 // cptr) at lists[cptr[c] / 64 ..], slots past the merged length set to 0;
 // flag[0] |= 1 if some row has entries left after len slots.

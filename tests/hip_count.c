@@ -13,7 +13,7 @@ static size_t used, most;
 static int (*real_malloc)(void **, size_t);
 static int (*real_free)(void *);
 static int (*real_instantiate)(void **, void *, void **, char *, size_t);
-static int graphs;
+static int graphs, mallocs;
 
 int count_init(const char *runtime)
 {
@@ -37,6 +37,7 @@ int hipMalloc(void **p, size_t n)
         slot[k].p = *p;
         slot[k].n = n;
         used += n;
+        ++mallocs;
         if (used > most)
             most = used;
         pthread_mutex_unlock(&mu);
@@ -66,6 +67,7 @@ int hipGraphInstantiate(void **exec, void *graph, void **node, char *log, size_t
 }
 
 int count_graphs(void) { return __atomic_load_n(&graphs, __ATOMIC_RELAXED); }
+int count_mallocs(void) { return mallocs; }
 size_t count_used(void) { return used; }
 size_t count_most(void) { return most; }
 void count_reset(void) { most = used; }
