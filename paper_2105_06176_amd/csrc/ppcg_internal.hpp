@@ -84,6 +84,18 @@ inline int fused_tile_rows(int n, int cus, int resident = kFusedResidentPerCU)
     }
     return best * kFusedThreads;
 }
+// Classic PCG with the CSR-vector SpMV: the smallest tiles of which one wave of
+// workgroups covers the system.  Its passes over a tile wait on one another's
+// gathers, so fewer workgroups leave the chip idle.  ms per solve with the rule
+// above, and with 2, 4, 8 and 16 tiles per compute unit: 700^2 5-point 17.3,
+// 12.1, 9.9, 9.8, 9.9; 100^3 27-point 33.9, 33.9, 24.5, 25.4, 25.3; 160^3
+// 7-point 31.4, 39.2, 31.3, 31.9, 34.0; 1.5 M random rows 9.8, 9.6, 9.8, 9.8, 9.9.
+inline int pcg_csrv_tile_rows(int n, int cus)
+{
+    const long long rows = (long long)kPcgResidentPerCU * (cus < 1 ? 1 : cus) * kFusedThreads;
+    const long long r = (n + rows - 1) / rows;
+    return (int)(r > kFusedRowsPerThread ? kFusedRowsPerThread : r) * kFusedThreads;
+}
 static_assert(kFusedThreads % kSellC == 0, "each wavefront of a fused tile reads whole SELL chunks");
 
 // Tile-to-workgroup mapping.  The fused update is a pure stream and runs
@@ -271,7 +283,7 @@ struct SysDesc {
     SysState *prs;        // classic PCG: the two scalar records of an iteration
     // single-launch iteration (ppcg_fused.hpp); unused by the two-launch form
     int nftiles;          // fused tiles (of frows rows)
-    int frows;            // rows per fused tile (fused_tile_rows(n, compute units))
+    int frows;            // rows per fused tile (fused_tile_rows, or pcg_csrv_tile_rows)
     SysState *frec;       // scalar state, 2 slots (launch parity)
     double *fpart;        // partial sums, 2 slots x nftiles x 4
     void *w1;             // second buffer of what the gathers read (w, or m for a diagonal that is not

@@ -537,16 +537,21 @@ ppcg_status fill_desc(ppcg_handle *h, int prec, SysState *st, SysDesc *d, double
     return PPCG_OK;
 }
 
-// Tiles of classic PCG's launches over a handle's system.
+// Rows and tiles of classic PCG's launches over a handle's system.
+static int pcg_tile_rows(const ppcg_handle *h)
+{
+    return h->fmt == FMT_CSRV ? pcg_csrv_tile_rows(h->n, h->cus) : fused_tile_rows(h->n, h->cus, kPcgResidentPerCU);
+}
+
 static int pcg_tiles(const ppcg_handle *h)
 {
-    const int fr = fused_tile_rows(h->n, h->cus, kPcgResidentPerCU);
+    const int fr = pcg_tile_rows(h);
     return (h->n + fr - 1) / fr;
 }
 
 static void set_pcg_tiles(const ppcg_handle *h, SysDesc *d)
 {
-    d->frows = fused_tile_rows(h->n, h->cus, kPcgResidentPerCU);
+    d->frows = pcg_tile_rows(h);
     d->nftiles = pcg_tiles(h);
 }
 
