@@ -59,15 +59,18 @@ constexpr int kPrepThreads = PPCG_SERVE_PREP_THREADS;
 // Large requests, whose iteration moves kLargeBytes and more, iterate together
 // only as far as one pass over them fits the memory-side cache: past it each
 // evicts the others' vectors, and all finish late.  Smaller ones pass a large
-// one that waits.  Prepared ahead: at most kReadyMost.  800 requests at once
-// (1,000 to 4 M rows), solves/s: all admitted (36 to 55 at a time) 80 to 83,
-// with 2 preparation threads (9 at a time) 93; in turn with 128 MB 102, 250 MB
-// 106, 400 MB 103, 1 GB 83; 16 prepared ahead 104.  At 66 requests/s the 99th
-// percentile went from 204 to 166 ms.
+// one that waits.  A large one is prepared with fewer than kReadyMost ahead of
+// it (with the same for small ones, 300 of up to 5,000 rows at once ran at 3,120
+// instead of 3,300 solves/s).  800 requests at once (1,000 to 4 M rows),
+// solves/s: all admitted (36 to 55 at a time) 80 to 83, with 2 preparation
+// threads (9 at a time) 93; in turn with 128 MB 102, 250 MB 106, 400 MB 103, 1 GB
+// 83; 16 prepared ahead 104.  At 66 requests/s the 99th percentile went from 204
+// to 175 ms.
 constexpr double kActiveBytes = kCacheBytes;
 constexpr double kLargeBytes = kActiveBytes / 16;
+constexpr int kLargeRows = (int)(kLargeBytes / 78.0);  // (fewest bytes of an FP64 iteration per row)
 constexpr int kReadyMost = kPrepThreads + 2;
-// automatic precision: smallest systems given reduced precision
+// automatic precision: smallest systems given reduced precision (see ppcg_srv_submit)
 #ifndef PPCG_AUTO_VALUES32_ROWS
 #define PPCG_AUTO_VALUES32_ROWS 65536
 #endif
@@ -166,9 +169,11 @@ static bool can_prepare(const ppcg_server *s)
     if (s->stop || s->prep_rc != PPCG_OK || s->queue.empty())
         return false;
     const int held = s->active + (int)s->ready.size() + s->preparing;
-    if (held >= kServerSlots || (int)s->ready.size() + s->preparing >= kReadyMost)
+    if (held >= kServerSlots)
         return false;
     const Request &r = s->reqs.at(s->queue.front());
+    if (r.n >= kLargeRows && (int)s->ready.size() + s->preparing >= kReadyMost)
+        return false;
     return (held == 0 && s->finishing == 0) || s->used + r.footprint <= s->budget;
 }
 
@@ -316,6 +321,8 @@ static void count_active(ppcg_server *s, const Request &r, int sign)
     s->active_bytes += sign * r.iter_bytes;
     if (r.iter_bytes >= kLargeBytes)
         s->large_bytes += sign * r.iter_bytes;
+    if (s->active == 0)
+        s->active_bytes = s->large_bytes = 0.0;  // (whatever the sums rounded to)
 }
 
 // Admit the prepared requests (calling thread, under `mu`): the large ones in
@@ -478,12 +485,16 @@ ppcg_status ppcg_srv_submit(ppcg_server *s, const ppcg_csr *A, const double *b, 
     const bool auto_prec = precision == PPCG_PRECISION_AUTO;
     ppcg_method method = s->defaults.method;
     if (auto_prec) {
-        // bytes of one iteration: FP64 PIPECG 12 per stored entry plus 17
-        // FP64 vector streams per row; FP32 values 8 per entry; classic PCG
-        // in FP32 8 per entry plus 12 FP32 vector streams per row, with two
-        // more launches per iteration (one-workgroup reductions), so it is
-        // taken only where the bytes saved clearly outweigh them; below
-        // 65536 rows launch latency, not bytes, sets the time
+        // bytes of one iteration on per-entry storage, which is what submission
+        // knows: FP64 PIPECG 12 per stored entry plus 17 FP64 vector streams
+        // per row; FP32 values 8 per entry; classic PCG in FP32 8 per entry
+        // plus 12 FP32 vector streams per row, taken where the bytes clearly
+        // favour it (its second launch waits for the first one's reduction);
+        // below 65536 rows launch latency, not bytes, sets the time.  On chunk
+        // lists, which the rule does not know of, FP64 reads no bytes per entry
+        // and is the faster choice: 198 distinct requests, 70 % of them
+        // constant-coefficient stencils, 112 to 115 solves/s all in FP64, 103 to
+        // 107 as chosen here (before the lists 78 to 83 and 81 to 85)
         const double b64 = 12.0 * (double)A->nnz + 136.0 * A->n;
         const double bv32 = 8.0 * (double)A->nnz + 136.0 * A->n;
         const double bp32 = 8.0 * (double)A->nnz + 48.0 * A->n;
