@@ -82,8 +82,9 @@ typedef enum {
                              a byte model of one iteration; FP64 PIPECG moves 12 bytes per
                              stored entry + 136 per row.  Systems of at least 262144 rows run
                              PPCG_MIXED_FP32 (Algorithm 1, 8 per entry + 48 per row) when
-                             that is at most 70% of FP64's bytes: enough to pay for its two
-                             extra launches per iteration.  Systems of at least 65536 rows
+                             that is at most 70% of FP64's bytes.  The model does not know of
+                             the chunk lists of constant-coefficient stencils, for which
+                             PPCG_FP64 is the faster request.  Systems of at least 65536 rows
                              run PPCG_MIXED_FP32_VALUES (8 per entry + 136 per row) when that
                              is at least 5% below FP64's.  Below 65536 rows launch latency,
                              not bytes, sets the time: PPCG_FP64.  A request run in reduced

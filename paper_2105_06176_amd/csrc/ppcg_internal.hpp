@@ -263,7 +263,8 @@ struct SysDesc {
                           // PIPECG SpMV reads them (else NULL)
     const int *pats;      // the distinct offset lists, concatenated
     // chunks described by lists alone (ppcg_stencil.hpp): per chunk {list
-    // start, mask start, length, 0}, or NULL
+    // start, mask start, length, length of the runs of consecutive columns
+    // that the list consists of (ppcg_lists.hpp) or 0}, or NULL
     const int4 *schunk;
     const int *soff;      // byte offset of each list entry's column from the row
     const double *sval;   // its value

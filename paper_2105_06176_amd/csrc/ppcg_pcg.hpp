@@ -2,8 +2,8 @@
 // III-A) on the device, for comparison with the pipelined method, and as the
 // iteration of the FP32-values mode when selected.
 //
-// One iteration is two launches over tiles of frows rows (as the single-launch
-// form of Algorithm 2, fused_tile_rows):
+// One iteration is two launches over tiles of frows rows (fused_tile_rows as the
+// single-launch form of Algorithm 2; pcg_csrv_tile_rows for CSR-vector rows):
 //
 //   k_pcg_spmv   every workgroup reduces the partial sums of (u, r), (u, u),
 //                (r, r) that the previous k_pcg_vma wrote and runs the
