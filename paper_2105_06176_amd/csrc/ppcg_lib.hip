@@ -259,9 +259,10 @@ static ppcg_status sell_size(hipStream_t s, int n, int sigma, const int *rowlen,
 // list is longer, its width grows to the list's length.  *ok is false (sz
 // unchanged) when some chunk's list passes k_sell_union_count's cap or the
 // widths grow by more than 1/32 in total: the lists would cost more padding
-// than they save.
+// than they save; or when the chunks before they grow hold more than `most`
+// entries.
 static ppcg_status widen_for_shared(hipStream_t s, int n, int nchunks, const int *rp, const int *ci, int64_t *sz,
-                                    bool *ok)
+                                    double most, bool *ok)
 {
     *ok = false;
     int *cnt = nullptr;
@@ -288,7 +289,7 @@ static ppcg_status widen_for_shared(hipStream_t s, int n, int nchunks, const int
         after += std::max<int64_t>(w, cnt_h[c]);
         sz_h[c] = std::max<int64_t>(w, cnt_h[c]) * kSellC;
     }
-    if (after * 32 > before * 33)
+    if (after * 32 > before * 33 || (double)(before * kSellC) > most)
         return PPCG_OK;
     PPCG_HIP(hipMemcpyAsync(sz, sz_h.data(), sizeof(int64_t) * nchunks, hipMemcpyHostToDevice, s));
     PPCG_HIP(hipStreamSynchronize(s));
@@ -362,9 +363,10 @@ static ppcg_status build_shared_lists(hipStream_t s, int n, const int *rp, const
 // SELL-C-sigma storage of the CSR matrix.  shared: when the rows keep their
 // order (sigma = 1) and every chunk has a shared offset list, the entries
 // are placed on the lists (k_sell_fill_shared); the products of every row,
-// and their order, stay those of its CSR entries.
+// and their order, stay those of its CSR entries.  shared_most: only on such
+// lists, of unsorted chunks with at most so many entries, else *out stays empty.
 static ppcg_status build_sell(hipStream_t s, int n, int sigma, const int *rp, const int *ci, const double *val,
-                              const int *rowlen, SellBuild *out, bool shared)
+                              const int *rowlen, SellBuild *out, bool shared, double shared_most = -1.0)
 {
     SellBuild sb;
     sb.sigma = sigma;
@@ -385,8 +387,9 @@ static ppcg_status build_sell(hipStream_t s, int n, int sigma, const int *rp, co
     k_chunk_size<<<blocks_for(sb.nchunks, 256), 256, 0, s>>>(n, sb.nchunks, sb.perm, rowlen, sz);
     bool widened = false;
     if (shared && sigma == 1) {
-        const ppcg_status rc = widen_for_shared(s, n, sb.nchunks, rp, ci, sz, &widened);
-        if (rc < 0) {
+        const ppcg_status rc =
+            widen_for_shared(s, n, sb.nchunks, rp, ci, sz, shared_most < 0.0 ? 1e300 : shared_most, &widened);
+        if (rc < 0 || (shared_most >= 0.0 && !widened)) {
             clean();
             return rc;
         }
@@ -1402,11 +1405,9 @@ static ppcg_status choose_format(ppcg_handle *h, const int *rp, const int *ci, c
     // Rows much shorter than their chunk's list go on to the timing.
     bool unsorted = false;  // the unsorted SELL layout is in place
     if (shared && !forced16 && h->dinv_const && !h->st_refused && h->opt.precision == PPCG_FP64) {
-        int64_t st1 = 0;
-        PPCG_TRY(sell_size(h->stream, h->n, 1, rowlen, &st1));
-        if ((double)st1 <= kListPadding * (double)h->nnz) {
-            SellBuild sb;
-            PPCG_TRY(build_sell(h->stream, h->n, 1, rp, ci, val, rowlen, &sb, shared));
+        SellBuild sb;
+        PPCG_TRY(build_sell(h->stream, h->n, 1, rp, ci, val, rowlen, &sb, shared, kListPadding * (double)h->nnz));
+        if (sb.col) {
             PPCG_TRY(adopt_sell(h, sb));
             PPCG_TRY(bind_f64(h, dinv_orig));
             PPCG_TRY(build_stencil(h, rp, ci));

@@ -17,7 +17,7 @@ torch.zeros(1, device="cuda")
 
 from paper_2105_06176_amd.ppcg import Solver  # noqa: E402
 from test_gpu_list_sample import unit_diagonal  # noqa: E402
-from workloads import random_spd, stencil27_lognormal  # noqa: E402
+from workloads import poisson2d, random_spd, stencil27_lognormal  # noqa: E402
 
 
 def allocations(A):
@@ -30,3 +30,4 @@ def allocations(A):
 for A in (random_spd(30000), stencil27_lognormal(30, seed=1)):
     allocations(A)  # the signature's choices are timed here
     print("COUNT", allocations(A), allocations(unit_diagonal(A)), flush=True)
+print("LISTS", allocations(poisson2d(64)), flush=True)

@@ -60,11 +60,14 @@ def test_automatic_choice(name):
 
 
 def test_no_layout_is_tried_in_vain(counter):  # noqa: F811
-    """The same pattern with a varying and a constant diagonal: as many allocations."""
+    """The same pattern with a varying and a constant diagonal: as many allocations.  A small matrix on lists: 19 (21 with
+    a sizing pass of its own)."""
     ppcg.lib()
     r = subprocess.run([sys.executable, HERE + "/create_count_run.py", counter, runtime()], capture_output=True,
                        text=True, timeout=100)
     assert r.returncode == 0, r.stderr[-2000:]
-    for line in r.stdout.split("COUNT")[1:]:
+    counts, lists = r.stdout.split("LISTS")
+    for line in counts.split("COUNT")[1:]:
         varying, constant = map(int, line.split()[:2])
         assert constant == varying, r.stdout
+    assert int(lists) <= 19, r.stdout
