@@ -28,7 +28,7 @@ alone = torch.empty(short.n, dtype=torch.float64)
 S.solve(torch.as_tensor(bs), out=alone)
 S.close()
 server = Server()
-rid = server.submit(long, bl, 1e-12, "fp64")
+rid = server.submit(long, bl, 0.0, "fp64")
 server.step()
 before = C.count_graphs()
 for _ in range(VISITS):
